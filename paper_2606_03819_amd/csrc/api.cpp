@@ -61,8 +61,8 @@ tf_status_t common_shapes(int b, int gamma, int d, int V, int k, bool rows_only 
     return TF_OK;
 }
 
-size_t stage1_bytes(int b, int gamma, int d, int V, bool bf16) {
-    return 256 + lm_scratch_bytes(b * gamma, V, d, bf16);
+size_t stage1_bytes(int b, int gamma, int d, int V, bool bf16, bool lean = false) {
+    return 256 + lm_scratch_bytes(lm_plan(b * gamma, V, d, bf16, lean), b * gamma, bf16);
 }
 
 }  // namespace
@@ -92,17 +92,17 @@ static tf_status_t check_marginal_args(const void* h, const void* lm_head, int b
 static tf_status_t marginal_topk(const void* h, const void* lm_head, int b, int gamma, int d, int V, int k,
                                  float inv_temperature, tf_dtype_t dt, int32_t* topk_idx, float* topk_logprob,
                                  float* lse, void* workspace, size_t workspace_bytes, hipStream_t stream,
-                                 hipEvent_t ev_begin, hipEvent_t ev_end) {
+                                 hipEvent_t ev_begin, hipEvent_t ev_end, bool lean = false) {
     const tf_status_t chk =
         check_marginal_args(h, lm_head, b, gamma, d, V, k, inv_temperature, dt, topk_idx, topk_logprob, lse);
     if (chk != TF_OK) return chk;
     const bool bf16 = dt == TF_BF16;
-    if (workspace == nullptr || !aligned16(workspace) || workspace_bytes < stage1_bytes(b, gamma, d, V, bf16))
+    if (workspace == nullptr || !aligned16(workspace) || workspace_bytes < stage1_bytes(b, gamma, d, V, bf16, lean))
         return TF_ERR_WORKSPACE;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     int* diag = reinterpret_cast<int*>(ws);
     const hipError_t e = launch_lmhead_topk(h, d, lm_head, b * gamma, d, V, k, inv_temperature, bf16, ws + 256,
-                                            topk_idx, topk_logprob, lse, diag, stream, ev_begin, ev_end);
+                                            topk_idx, topk_logprob, lse, diag, stream, ev_begin, ev_end, lean);
     return e == hipSuccess ? TF_OK : TF_ERR_HIP;
 }
 
@@ -159,11 +159,13 @@ tf_status_t treeflash_marginal_topk_static(const void* h, const void* lm_head, i
     const tf_status_t chk =
         check_marginal_args(h, lm_head, b, gamma, d, V, k, inv_temperature, dt, topk_idx, topk_logprob, lse);
     if (chk != TF_OK) return chk;
-    if (stage1_bytes(b, gamma, d, V, dt == TF_BF16) > kStaticScratchBytes) return TF_ERR_WORKSPACE;
+    // the plan with the fewest partials where the usual one's do not fit
+    const bool lean = stage1_bytes(b, gamma, d, V, dt == TF_BF16) > kStaticScratchBytes;
+    if (lean && stage1_bytes(b, gamma, d, V, dt == TF_BF16, true) > kStaticScratchBytes) return TF_ERR_WORKSPACE;
     void* ws = device_scratch();
     if (ws == nullptr) return TF_ERR_HIP;
     return marginal_topk(h, lm_head, b, gamma, d, V, k, inv_temperature, dt, topk_idx, topk_logprob, lse, ws,
-                         kStaticScratchBytes, stream, nullptr, nullptr);
+                         kStaticScratchBytes, stream, nullptr, nullptr, lean);
 }
 
 size_t treeflash_static_scratch_bytes(void) { return kStaticScratchBytes; }

@@ -22,6 +22,15 @@ __device__ __forceinline__ void dma16(const void* src, void* dst, int cpol) {
         __builtin_amdgcn_global_load_lds((global_void_t*)src, (lds_void_t*)dst, 16, 0, 0);
 }
 
+// The same through a buffer descriptor: 16 bytes a lane at byte offset `voff`
+// (per lane) + `soff` (uniform); offsets past the descriptor give zeros.
+__device__ __forceinline__ void buffer_dma16(__amdgpu_buffer_rsrc_t rs, unsigned voff, int soff, void* dst, int cpol) {
+    if (cpol == kCpolNt)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff, soff, 0, kCpolNt);
+    else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)dst, 16, voff, soff, 0, 0);
+}
+
 // wait until at most N of this wave's memory loads are outstanding (also a
 // compiler barrier for memory operations)
 template <int N>

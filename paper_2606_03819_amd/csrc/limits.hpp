@@ -21,12 +21,18 @@ constexpr int part_stride(int keep) { return 4 + 2 * keep; }
 // list for the same rate of overflowing lanes).
 constexpr int kLane = 4;
 constexpr int kLaneMfma = 2;
-// 256-row blocks (the batched steps: thousands of rows, so a lane holding
-// three of a row's best 32 logits, which a two-entry list flags for the
-// exact slow path, turns up in a sizeable share of launches)
-constexpr int kLaneMfmaMulti = 3;
 constexpr int kLaneMfmaLong = 3;
 constexpr int kLaneMfmaWide = 3;
 constexpr int kLaneMfmaWideLong = 5;
+
+// Block-tiled kernel (lm_tile.hpp): keys a lane ranks of its 24-32 logits of
+// a row; a slice is re-evaluated when the last of them may hide one of the
+// row's best k.
+constexpr int kLaneTile = 4;
+constexpr int kLaneTileLong = 5;
+
+// Largest byte span a buffer descriptor of the block-tiled GEMM covers; an
+// offset with this bit set is out of range and reads zeros.
+constexpr unsigned kTileSpan = 1u << 30;
 
 }  // namespace tf

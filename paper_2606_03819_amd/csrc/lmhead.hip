@@ -8,6 +8,7 @@
 #include "launch.hpp"
 #include "plan.hpp"
 #include "stream_gemm.hpp"
+#include "tile_gemm.hpp"
 
 namespace tf {
 
@@ -476,6 +477,60 @@ __device__ __forceinline__ void slice_logits(const uint16_t* xr, const uint16_t*
             for (int j = 0; j < 16; ++j) colv[(wave + 4 * i) * 32 + acc_row(j, lane)] = lg[i][j];
 }
 
+// The same for the block-tiled kernel's chain (one MFMA 16x16x32 per 32-wide
+// k block in increasing k, zeros past d): wave w takes tiles tg + w, tg + w +
+// 4, ..., one at a time as two tiles of 16 vocabulary rows, so that the merge
+// kernel's registers stay those of its usual path (1936 rows: 25 us; with
+// four tiles at once 45, half the workgroups fitting a CU).
+__device__ __forceinline__ void slice_logits16(const uint16_t* xr, const uint16_t* w, int d, int V, int tg, int tend,
+                                               float* colv) {
+    constexpr int P = 3;   // k blocks of loads in flight, twice
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k8 = 8 * (lane >> 4);
+    const int nblk = (d + 31) / 32;
+    for (int t = tg + wave; t < tend; t += 4) {
+        const uint16_t* wp[2];
+        f32x4 acc[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            wp[i] = w + (size_t)min(t * 32 + 16 * i + (lane & 15), V - 1) * d;
+            acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto load = [&](int blk, u32x4 (&xv)[P], u32x4 (&wv)[2][P]) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const int k = (blk + p) * 32 + k8;
+                const int kc = min(k, d - 8);   // in bounds; zeroed on the activation side past d
+                xv[p] = *reinterpret_cast<const u32x4*>(xr + kc);
+                if (k >= d) xv[p] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int i = 0; i < 2; ++i) wv[i][p] = *reinterpret_cast<const u32x4*>(wp[i] + kc);
+            }
+        };
+        auto mma = [&](int blk, const u32x4 (&xv)[P], const u32x4 (&wv)[2][P]) {
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (blk + p < nblk)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) acc[i] = mfma_16x16x32_bf16(wv[i][p], xv[p], acc[i]);
+        };
+        u32x4 xa[P], wa[2][P], xb[P], wb[2][P];
+        load(0, xa, wa);
+        for (int blk = 0; blk < nblk; blk += 2 * P) {
+            load(blk + P, xb, wb);
+            mma(blk, xa, wa);
+            if (blk + 2 * P < nblk) load(blk + 2 * P, xa, wa);
+            mma(blk + P, xb, wb);
+        }
+        // every column holds the row's logits: lane 16 q has rows 4 q .. 4 q + 3
+        if ((lane & 15) == 0)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) colv[(t - tg) * 32 + 16 * i + 4 * (lane >> 4) + j] = acc[i][j];
+    }
+}
+
 __device__ __forceinline__ float dot_row(const float* a, const float* b, int d) {
     float acc = 0.f;
     for (int k = 0; k < d; ++k) acc = fmaf(a[k], b[k], acc);
@@ -626,8 +681,9 @@ static_assert(kMaxSplitsLong * kKeepLong <= kMergeCap, "long-list slices fit the
 //     value is re-evaluated exactly from memory, so the result is the exact
 //     top-k of the row for any data, ties included.
 // SPT: slices per thread (nsplit <= 256 * SPT), so that a launch with few
-// slices keeps no idle slice slots in its registers.
-template <class T, int KEEP, int SPT>
+// slices keeps no idle slice slots in its registers.  TILE: the partials come
+// from the block-tiled kernel, whose chain the re-evaluation then runs.
+template <class T, int KEEP, int SPT, bool TILE = false>
 __global__ __launch_bounds__(256) void merge_topk_kernel(MergeArgs a) {
     constexpr int PS = part_stride(KEEP);
     constexpr int NQ = PS / 4;   // 16-byte words of one partial
@@ -851,7 +907,9 @@ __global__ __launch_bounds__(256) void merge_topk_kernel(MergeArgs a) {
             for (int tg = t0s; tg < t1s; tg += 16) {
                 const int tend = min(t1s, tg + 16);
                 const int v0 = tg * 32, v1 = min(a.V, tend * 32);
-                if constexpr (sizeof(T) == 2) {
+                if constexpr (TILE) {
+                    slice_logits16(xr, wb, a.d, a.V, tg, tend, s_colv);
+                } else if constexpr (sizeof(T) == 2) {
                     const int ntl = (tend - tg + 3) / 4;   // tiles per wave
                     if (ntl == 1)
                         slice_logits<1>(xr, wb, a.d, a.V, tg, tend, s_colv);
@@ -958,18 +1016,12 @@ static hipError_t dispatch_lm_bf16(const LmPlan& p, const uint16_t* x, long ldx,
         if (p.NT == 1)
             return launch_lm_dma<LONG, TF_LM_DMA_NT1_WM, 1, TF_LM_DMA_NT1_NW, TF_LM_DMA_KC, true>(x, ldx, w, sh, p.map, nb,
                                                                                             V, sl2, part, diag, st);
-        if (p.grid && p.NT == 2)   // 33..64 rows: one activation tile per wave of the grid
+        if (p.NT == 2)   // 33..64 rows: one activation tile per wave of the grid
             return launch_lm_dma<LONG, TF_LM_DMA_WM, 2, TF_LM_DMA_NW_SINGLE, TF_LM_DMA_KC, true, 1, TF_LM_DMA_SINGLE_WB>(
                 x, ldx, w, sh, p.map, nb, V, sl2, part, diag, st);
-        if (p.grid && p.wnt)   // a single row block
-            return launch_lm_dma<LONG, TF_LM_DMA_WM, 4, TF_LM_DMA_NW_SINGLE, TF_LM_DMA_KC, true, 1, TF_LM_DMA_SINGLE_WB>(
-                x, ldx, w, sh, p.map, nb, V, sl2, part, diag, st);
-        if (p.grid)   // a few row blocks sharing each range's weights through L2
-            return launch_lm_dma<LONG, TF_LM_DMA_WM, 4, TF_LM_DMA_NW_SINGLE, TF_LM_DMA_KC, false, 1, TF_LM_DMA_SINGLE_WB>(
-                x, ldx, w, sh, p.map, nb, V, sl2, part, diag, st);
-        // several row blocks: 256-row blocks (lm_plan)
-        return launch_lm_dma<LONG, TF_LM_DMA_MULTI_WM, 8, 8, TF_LM_DMA_KC, false, 1, 2>(x, ldx, w, sh, p.map, nb, V,
-                                                                                    sl2, part, diag, st);
+        // 65 rows up: one row block, or the lean plan's two
+        return launch_lm_dma<LONG, TF_LM_DMA_WM, 4, TF_LM_DMA_NW_SINGLE, TF_LM_DMA_KC, true, 1, TF_LM_DMA_SINGLE_WB>(
+            x, ldx, w, sh, p.map, nb, V, sl2, part, diag, st);
     }
     if (p.NT == 1)
         launch_lm_bf16<LONG, TF_LM_WM_NT1, 1, TF_LM_NW_NT1, TF_PIPE_DEFAULT, true>(x, ldx, w, sh, p.map, nb, V, sl2, part,
@@ -989,8 +1041,8 @@ static hipError_t dispatch_lm_bf16(const LmPlan& p, const uint16_t* x, long ldx,
 hipError_t launch_lmhead_topk(const void* x, long ldx, const void* w, int rows, int d, int V, int K,
                               float inv_t, bool bf16, unsigned char* lm_ws, int32_t* out_idx, float* out_lp,
                               float* out_lse, int* diag, hipStream_t stream, hipEvent_t ev_begin,
-                              hipEvent_t ev_end) {
-    const LmPlan p = lm_plan(rows, V, d, bf16);
+                              hipEvent_t ev_end, bool lean) {
+    const LmPlan p = lm_plan(rows, V, d, bf16, lean);
     if (p.nsplit() > kMaxSplits) return hipErrorInvalidValue;
     float* part = reinterpret_cast<float*>(lm_ws);
     // the LM kernels read R, K, ntiles, nrb and nk; G counts workgroups
@@ -998,7 +1050,11 @@ hipError_t launch_lmhead_topk(const void* x, long ldx, const void* w, int rows, 
     const float sl2 = inv_t * kLog2e;
     if (ev_begin != nullptr && hipEventRecord(ev_begin, stream) != hipSuccess) return hipErrorInvalidHandle;
     const bool longl = lm_long_lists(p, bf16, K);
-    if (bf16) {
+    if (p.tile) {
+        const hipError_t te = launch_lm_tile(p, static_cast<const uint16_t*>(x), ldx, static_cast<const uint16_t*>(w),
+                                             rows, d, V, longl, sl2, part, diag, stream);
+        if (te != hipSuccess) return te;
+    } else if (bf16) {
         const hipError_t de =
             longl ? dispatch_lm_bf16<true>(p, static_cast<const uint16_t*>(x), ldx, static_cast<const uint16_t*>(w),
                                            sh, V, sl2, part, diag, stream)
@@ -1014,23 +1070,33 @@ hipError_t launch_lmhead_topk(const void* x, long ldx, const void* w, int rows, 
     MergeArgs ma{part, p.nsplit(), p.map, K, V, d, inv_t, sl2, out_idx, out_lp, out_lse, x, ldx, w, diag};
     // slices per thread: two, four or the most a launch may have
     const int ns = p.nsplit();
-    if (bf16 && longl) {
-        if (ns <= 512)
-            hipLaunchKernelGGL((merge_topk_kernel<uint16_t, kKeepLong, 2>), dim3(rows), dim3(256), 0, stream, ma);
-        else
-            hipLaunchKernelGGL((merge_topk_kernel<uint16_t, kKeepLong, kMaxSplitsLong / 256>), dim3(rows), dim3(256),
-                               0, stream, ma);
-    } else if (bf16) {
-        if (ns <= 512)
-            hipLaunchKernelGGL((merge_topk_kernel<uint16_t, kKeep, 2>), dim3(rows), dim3(256), 0, stream, ma);
+#define TF_MERGE(...) hipLaunchKernelGGL((merge_topk_kernel<__VA_ARGS__>), dim3(rows), dim3(256), 0, stream, ma)
+    if (!bf16) {
+        TF_MERGE(float, kKeep, kMaxSplits / 256);
+    } else if (p.tile) {
+        if (longl && ns <= 512)
+            TF_MERGE(uint16_t, kKeepLong, 2, true);
+        else if (longl)
+            TF_MERGE(uint16_t, kKeepLong, kMaxSplitsLong / 256, true);
+        else if (ns <= 512)
+            TF_MERGE(uint16_t, kKeep, 2, true);
         else if (ns <= 1024)
-            hipLaunchKernelGGL((merge_topk_kernel<uint16_t, kKeep, 4>), dim3(rows), dim3(256), 0, stream, ma);
+            TF_MERGE(uint16_t, kKeep, 4, true);
         else
-            hipLaunchKernelGGL((merge_topk_kernel<uint16_t, kKeep, kMaxSplits / 256>), dim3(rows), dim3(256), 0,
-                               stream, ma);
+            TF_MERGE(uint16_t, kKeep, kMaxSplits / 256, true);
     } else {
-        hipLaunchKernelGGL((merge_topk_kernel<float, kKeep, kMaxSplits / 256>), dim3(rows), dim3(256), 0, stream, ma);
+        if (longl && ns <= 512)
+            TF_MERGE(uint16_t, kKeepLong, 2);
+        else if (longl)
+            TF_MERGE(uint16_t, kKeepLong, kMaxSplitsLong / 256);
+        else if (ns <= 512)
+            TF_MERGE(uint16_t, kKeep, 2);
+        else if (ns <= 1024)
+            TF_MERGE(uint16_t, kKeep, 4);
+        else
+            TF_MERGE(uint16_t, kKeep, kMaxSplits / 256);
     }
+#undef TF_MERGE
     return hipGetLastError();
 }
 

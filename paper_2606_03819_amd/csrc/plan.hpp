@@ -115,17 +115,19 @@ inline GemmPlan gemm_plan(int rows, int ntiles, int K, int wg_single) {
 // LM head over [rows, d] x [V, d]: vocabulary slices (see SliceMap), one
 // workgroup per (tile range, row block), the row blocks of a range on
 // consecutive workgroups so that they share its tiles through L2.  One row
-// block, or up to TF_LM_GRID_NRB on the DMA kernel's wave grid: the tiles
-// spread over TF_LM_WORKGROUPS workgroups in all; more row blocks: one
-// chunk per range.  fp32 (small workloads, SIMT kernel): 32 rows and at most
+// block: the tiles spread over TF_LM_WORKGROUPS workgroups; more row blocks:
+// the block-tiled plan above.  fp32 (small workloads, SIMT kernel): 32 rows and at most
 // 8 tiles (256 tokens) per workgroup.
 struct LmPlan {
     int NT, WM, NW, chunk, nrb, ntiles, nk;
     int WB = 1;   // waves along the activation tiles (a grid of NW / WB x WB waves)
-    bool grid = false;   // the DMA kernel's 2 x 2 wave grid (up to TF_LM_GRID_NRB row blocks)
+    bool grid = false;   // the DMA kernel's 2 x 2 wave grid (33 rows up)
     SliceMap map;
     bool wnt;
-    bool dma;   // the LDS-DMA kernel (32-row tiles, the grid, or 256-row blocks)
+    bool dma;   // the LDS-DMA kernel (32-row tiles or the grid)
+    // the block-tiled kernel (tile_gemm.hpp): WM and NT count 16-row tiles of
+    // one of its 2 x 2 waves
+    bool tile = false;
     int nsplit() const { return map.G * map.rmax; }
     int blocks() const { return map.G * nrb; }
 };
@@ -166,23 +168,6 @@ struct LmPlan {
 #ifndef TF_LM_DMA_SINGLE_WB
 #define TF_LM_DMA_SINGLE_WB 2
 #endif
-// Row blocks up to which the grid shape serves the LM head: the row blocks
-// of a tile range run on consecutive workgroups (one XCD), so the second
-// reads the weights the first brought into L2 (plain loads, not
-// non-temporal).
-#ifndef TF_LM_GRID_NRB
-#define TF_LM_GRID_NRB 2
-#endif
-// Several row blocks (MFMA-bound): 256-row blocks of eight waves in a 4 x 2
-// grid (2 weight x 4 activation tiles each), one workgroup per CU.  Each
-// copied weight tile then meets 256 activation rows and each copied
-// activation tile 8 weight tiles: 0.5 KiB of copies per 32 x 32 tile pair of
-// MFMA work against 0.75 KiB with 128-row blocks of four waves (+6% on the
-// 1936-row batched step); 64-wide k steps fill the 160 KiB of LDS (+1.5%
-// against 32-wide).
-#ifndef TF_LM_DMA_MULTI_WM
-#define TF_LM_DMA_MULTI_WM 2
-#endif
 #ifndef TF_LM_DMA_KC
 #define TF_LM_DMA_KC 64
 #endif
@@ -201,19 +186,65 @@ struct LmPlan {
 inline int lm_nw(int NT) { return NT == 1 ? TF_LM_NW_NT1 : (NT == 2 ? TF_LM_NW_NT2 : TF_LM_NW_NT4); }
 inline int lm_wm(int NT) { return NT == 1 ? TF_LM_WM_NT1 : (NT == 2 ? TF_LM_WM_NT2 : TF_LM_WM_NT4); }
 
-inline LmPlan lm_plan(int rows, int V, int d, bool bf16) {
+// The block-tiled kernel serves bf16 calls of more rows than one 128-row block
+// (widths up to kTileMaxK keep its byte offsets in 30 bits).
+constexpr int kTileMinRows = 129;
+constexpr int kTileMaxK = 1 << 20;
+
+// Row blocks of at most 256 rows, 192 where the rows then fill them (a wave
+// grid of 2 x 2 waves of 16-row tiles: NXT = 8 or 6).  One row block streams
+// the vocabulary once and is as much HBM- as MFMA-bound: the tiles are spread
+// evenly over the CUs, in rounds of 6, 7 or 8 tiles, whichever leaves the
+// least work for padding (a round's epilogue counted as one more tile), while
+// that makes no more slices than long lists may have.  Otherwise, and for
+// more row blocks: one slice of 8 tiles per workgroup.
+inline LmPlan lm_tile_plan(int rows, int V, int d) {
+    LmPlan p;
+    p.ntiles = cdiv(V, 32);
+    p.nk = cdiv(d, 64);
+    p.dma = false;
+    p.tile = true;
+    p.nrb = cdiv(rows, 256);
+    p.NT = cdiv(rows, p.nrb * 32) <= 6 ? 6 : 8;
+    p.nrb = cdiv(rows, 32 * p.NT);
+    p.NW = 4;
+    p.WB = 2;
+    p.WM = 8;
+    p.wnt = p.nrb == 1;
+    if (p.nrb == 1) {
+        const int G = p.ntiles < kNumCUs ? p.ntiles : kNumCUs;
+        const int per = cdiv(p.ntiles, G);
+        for (int wm = 7; wm >= 6; --wm)
+            if (cdiv(per, wm) * (wm + 1) < cdiv(per, p.WM) * (p.WM + 1)) p.WM = wm;
+        p.map = make_slice_map(p.ntiles, G, p.WM);
+    }
+    if (p.nrb > 1 || p.nsplit() > kMaxSplitsLong) {
+        p.WM = 8;
+        p.map = make_slice_map(p.ntiles, cdiv(p.ntiles, 8), 8);
+    }
+    p.chunk = p.WM;
+    return p;
+}
+
+// `lean`: the plan with the fewest slices (and so partials) for 129-256 rows,
+// for callers whose scratch is short; also taken for vocabularies whose
+// block-tiled slices would be too many for long lists.
+inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
+    if (bf16 && rows >= kTileMinRows && d <= kTileMaxK) {
+        const LmPlan t = lm_tile_plan(rows, V, d);
+        if (rows > 256 || (!lean && t.nsplit() <= kMaxSplitsLong)) return t;
+    }
     LmPlan p;
     p.ntiles = cdiv(V, 32);
     p.nk = cdiv(d, 64);
     p.dma = false;
     if (bf16) {
         p.NT = plan_nt(rows);
-        // k in whole 64-wide steps: the DMA kernel -- 32-row tiles, the 2 x 2
-        // wave grid up to TF_LM_GRID_NRB row blocks, else 256-row blocks
+        // k in whole 64-wide steps: the DMA kernel -- 32-row tiles, or the
+        // 2 x 2 wave grid (two row blocks: the lean plan)
         p.nrb = cdiv(rows, 32 * p.NT);
-        p.grid = p.NT >= 2 && p.nrb <= TF_LM_GRID_NRB && d % TF_LM_DMA_KC == 0;
-        const bool multi = p.NT == 4 && p.nrb > 1 && !p.grid && d % TF_LM_DMA_KC == 0;
-        p.dma = p.grid || multi || (p.NT == 1 && d % TF_LM_DMA_KC == 0);
+        p.grid = p.NT >= 2 && p.nrb <= 2 && d % TF_LM_DMA_KC == 0;
+        p.dma = p.grid || (p.NT == 1 && d % TF_LM_DMA_KC == 0);
         if (p.dma && p.NT == 1) {
             p.WM = TF_LM_DMA_NT1_WM;
             p.NW = TF_LM_DMA_NT1_NW;
@@ -221,21 +252,13 @@ inline LmPlan lm_plan(int rows, int V, int d, bool bf16) {
             p.WM = TF_LM_DMA_WM;
             p.NW = TF_LM_DMA_NW_SINGLE;
             p.WB = TF_LM_DMA_SINGLE_WB;
-        } else if (p.dma) {
-            // 256-row blocks: eight waves in a 4 x 2 grid of 2 weight x 4
-            // activation tiles, one workgroup per CU
-            p.NT = 8;
-            p.nrb = cdiv(rows, 256);
-            p.WM = TF_LM_DMA_MULTI_WM;
-            p.NW = 8;
-            p.WB = 2;
         } else {
             p.WM = lm_wm(p.NT);
             p.NW = lm_nw(p.NT);
         }
         p.chunk = p.NW / p.WB * p.WM;
-        // one row block, or the grid kernel: TF_LM_WORKGROUPS workgroups in
-        // all, the row blocks of a tile range on consecutive ones
+        // one row block, or the grid: TF_LM_WORKGROUPS workgroups in all;
+        // else one chunk per range
         const int gw = TF_LM_WORKGROUPS / p.nrb;
         const int G = p.nrb == 1 || p.grid ? (p.ntiles < gw ? p.ntiles : gw) : cdiv(p.ntiles, p.chunk);
         p.map = make_slice_map(p.ntiles, G, p.chunk);
@@ -386,10 +409,12 @@ inline bool lm_long_lists(const LmPlan& p, bool bf16, int K) {
 
 // LM-head scratch: the (row, slice) partials, sized for the long lists
 // whenever a launch could keep them.
-inline size_t lm_scratch_bytes(int rows, int V, int d, bool bf16) {
-    const LmPlan p = lm_plan(rows, V, d, bf16);
+inline size_t lm_scratch_bytes(const LmPlan& p, int rows, bool bf16) {
     const int stride = bf16 && p.nsplit() <= kMaxSplitsLong ? kPartStrideLong : kPartStride;
     return align256((size_t)rows * p.nsplit() * stride * 4);
+}
+inline size_t lm_scratch_bytes(int rows, int V, int d, bool bf16) {
+    return lm_scratch_bytes(lm_plan(rows, V, d, bf16), rows, bf16);
 }
 
 struct Workspace {

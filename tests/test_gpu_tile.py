@@ -1,0 +1,61 @@
+"""The LM head's block-tiled kernel (more than 128 rows) on small shapes.
+
+Operands are small integers (and a power of two), so every logit is exact in
+any order of the sums and carries many ties: the lists must equal a stable
+sort by (value desc, id asc) entry by entry, which exercises the lane, wave
+and workgroup merges, the bounds and the exact re-evaluation of the kernel's
+own chain.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(rows, V, d, seed, spread):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    h = torch.randint(-2, 3, (1, rows, d), generator=g, device="cuda").to(torch.bfloat16)
+    lm = torch.randint(-spread, spread + 1, (V, d), generator=g, device="cuda").to(torch.bfloat16) * 0.25
+    return h, lm
+
+
+def _check(h, lm, k, idx, lp, lse):
+    import torch
+    y = h[0].double() @ lm.double().t()
+    want = torch.sort(y, dim=1, descending=True, stable=True)
+    assert torch.equal(idx[0].long(), want.indices[:, :k]), "ids are not the stable sort's"
+    ref_lse = torch.logsumexp(y, 1)
+    # fp32 sums of at most V exponentials and one logarithm
+    assert (lse[0].double() - ref_lse).abs().max() <= 1e-4
+    assert (lp[0].double() - (want.values[:, :k] - ref_lse[:, None])).abs().max() <= 1e-4
+
+
+# row blocks of 192 and 256 rows and their remainders; slices of 6, 7 and 8
+# tiles, several rounds, a ragged last tile; k steps with a tail (d % 64) and
+# fewer steps than the rings hold; short and long lists
+@pytest.mark.parametrize("rows,V,d,k", [
+    (129, 8193, 64, 8), (192, 20011, 16, 32), (193, 57344, 80, 32), (256, 65536 + 31, 128, 64),
+    (241, 50021, 112, 100), (257, 5003, 192, 32), (384, 3001, 48, 64), (385, 9000, 1040, 16), (513, 300, 320, 300),
+    (700, 33, 64, 5),
+])
+def test_lm_head_tile_is_the_stable_sort(rows, V, d, k):
+    import torch
+    from paper_2606_03819_amd import binding
+    h, lm = _case(rows, V, d, rows + V, 2 if d < 512 else 1)
+    lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
+    idx, lp = binding.treeflash_marginal_topk(h, lm, k, lse=lse)
+    _check(h, lm, k, idx, lp, lse)
+
+
+def test_lm_head_tile_against_the_lean_plan():
+    """The static-scratch call keeps fitting 16 MiB by the plan with fewer slices."""
+    import torch
+    from paper_2606_03819_amd import binding
+    rows, V, d, k = 256, 170001, 64, 32
+    h, lm = _case(rows, V, d, 7, 2)
+    lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
+    idx, lp = binding.treeflash_marginal_topk_static(h, lm, k, lse=lse)
+    _check(h, lm, k, idx, lp, lse)
+    lse2 = torch.empty_like(lse)
+    idx2, lp2 = binding.treeflash_marginal_topk(h, lm, k, lse=lse2)
+    assert torch.equal(idx, idx2) and (lse - lse2).abs().max() <= 1e-4
