@@ -44,8 +44,6 @@ __global__ __launch_bounds__(64 * NW, 1) void lmhead_bf16_kernel(const uint16_t*
         seg.kc0 = 0;
         seg.kc1 = sh.nk;
         seg.row0 = rb * Tr::TR;
-        seg.gfirst = L;
-        seg.npieces = 1;
         if (seg.t0 == seg.t1) {   // empty slice: a partial the merge skips
             const int t = threadIdx.x;
             if (t < Tr::TR && seg.row0 + t < sh.R) {
@@ -150,8 +148,6 @@ __global__ __launch_bounds__(64 * NW, MINB) void lmhead_dma_kernel(const uint16_
         seg.kc0 = 0;
         seg.kc1 = sh.nk;
         seg.row0 = rb * 32 * NT;
-        seg.gfirst = L;
-        seg.npieces = 1;
         if (seg.t0 == seg.t1) {   // empty slice: a partial the merge skips
             const int t = threadIdx.x;
             if (t < 32 * NT && seg.row0 + t < sh.R) {

@@ -9,7 +9,7 @@
 #include "mlp_dma.hpp"
 #include "plan.hpp"
 #include "rows.hpp"
-#include "stream_gemm.hpp"
+#include "tile_product.hpp"
 
 namespace tf {
 
@@ -157,20 +157,24 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_bf16_kernel(const uint16_t* 
     }
 }
 
-// ------------------------------------------------------------------ bf16
-
-// Any product of the approximator over several row blocks: `ws` weight rows
-// against `xs` activation rows, the epilogue behind the split-k fix-up.
-template <int WM, int NT, int NW, int PIPE, bool WNT, class WSrc, class XSrc, class Epi>
-__global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void product_bf16_kernel(WSrc ws, XSrc xs, GemmShape sh,
-                                                                              Epi epi) {
-    __shared__ __align__(16) unsigned char smem[GemmTraits<WM, NT, NW>::SMEM_BYTES];
-    stream_gemm<WM, NT, NW, PIPE, WNT>(ws, xs, epi, sh, smem);
-}
-
 // ------------------------------------------------------------------ fp32
 
-// The approximator's fp32 products (small models): out[r, n] = epi( x_r . W[n] )
+// one activation: fp32, or a bf16 hi/lo pair interleaved by 8
+__device__ __forceinline__ float load_act(const float* p, size_t i) { return p[i]; }
+__device__ __forceinline__ float load_act(const uint16_t* p, size_t i) {
+    const size_t q = (i >> 3) * 16 + (i & 7);
+    return bf16_bits_to_f32(p[q]) + bf16_bits_to_f32(p[q + 8]);
+}
+__device__ __forceinline__ void store_act(float* p, size_t i, float v) { p[i] = v; }
+__device__ __forceinline__ void store_act(uint16_t* p, size_t i, float v) {
+    const size_t q = (i >> 3) * 16 + (i & 7);
+    const uint32_t hi = f32_to_bf16_bits(v);
+    p[q] = (uint16_t)hi;
+    p[q + 8] = (uint16_t)f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+}
+
+// The approximator's fp32 products (small models), and the bf16 ones whose
+// widths pass the block-tiled kernel's offsets (tile_width_ok): out[r, n] = epi( x_r . W[n] )
 // with x_r = [x0 row of r's drafter state (d0 wide) ; x1 row r (K - d0 wide)].
 // A workgroup holds 16 rows x 16 output columns; the reduction range streams
 // through LDS in 64-wide chunks (every thread copies four activation and four
@@ -179,12 +183,12 @@ __global__ __launch_bounds__(64 * NW, 512 / (64 * NW)) void product_bf16_kernel(
 // accumulates its output with one fmaf chain in k order.
 //   GATE:  act = silu(x . W_gate[n]) * (x . W_up[n])  (W_up null: silu alone)
 //   else:  out = h[r's drafter state, n] + x . W[n]   (down projection, linear)
-template <bool GATE>
-__global__ __launch_bounds__(256) void mlp_f32_kernel(const float* __restrict__ wa, const float* __restrict__ wb,
-                                                      int N, int K, const float* __restrict__ x0, int d0,
-                                                      const float* __restrict__ x1, int ld1, RowTable rt, int rows,
-                                                      const float* __restrict__ h, float* __restrict__ out,
-                                                      int ldo) {
+// ACT: x1 holds activations (load_act).
+template <class T, bool GATE, bool ACT = false>
+__global__ __launch_bounds__(256) void mlp_simt_kernel(const T* __restrict__ wa, const T* __restrict__ wb, int N,
+                                                       long K, const T* __restrict__ x0, int d0,
+                                                       const T* __restrict__ x1, long ld1, RowTable rt, int rows,
+                                                       const T* __restrict__ h, T* __restrict__ out, int ldo) {
     __shared__ float xs[16][65];
     __shared__ float ws[2][16][65];
     const int tid = threadIdx.x;
@@ -204,23 +208,29 @@ __global__ __launch_bounds__(256) void mlp_f32_kernel(const float* __restrict__ 
         xrow[j] = r < rows ? state_of(r) : -1;
     }
     float px[4], pw[4], pw2[4];
-    auto fetch = [&](int k0) {
+    auto fetch = [&](long k0) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int e = tid + 256 * j;
-            const int rr = e >> 6, k = k0 + (e & 63);
+            const int rr = e >> 6;
+            const long k = k0 + (e & 63);
             const int r = r0 + rr, n = n0 + rr;
             px[j] = pw[j] = pw2[j] = 0.f;
-            if (xrow[j] >= 0 && k < K) px[j] = k < d0 ? x0[(size_t)xrow[j] * d0 + k] : x1[(size_t)r * ld1 + (k - d0)];
+            if (xrow[j] >= 0 && k < K) {
+                if constexpr (ACT)
+                    px[j] = load_act(x1, (size_t)r * ld1 + k);
+                else
+                    px[j] = k < d0 ? load_elem(x0, (size_t)xrow[j] * d0 + k) : load_elem(x1, (size_t)r * ld1 + (k - d0));
+            }
             if (n < N && k < K) {
-                pw[j] = wa[(size_t)n * K + k];
-                if (two) pw2[j] = wb[(size_t)n * K + k];
+                pw[j] = load_elem(wa, (size_t)n * K + k);
+                if (two) pw2[j] = load_elem(wb, (size_t)n * K + k);
             }
         }
     };
     float acc_a = 0.f, acc_b = 0.f;
     fetch(0);
-    for (int k0 = 0; k0 < K; k0 += 64) {
+    for (long k0 = 0; k0 < K; k0 += 64) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int e = tid + 256 * j;
@@ -230,7 +240,7 @@ __global__ __launch_bounds__(256) void mlp_f32_kernel(const float* __restrict__ 
         }
         __syncthreads();
         if (k0 + 64 < K) fetch(k0 + 64);   // the next chunk's loads run under this chunk's products
-        const int kn = min(64, K - k0);
+        const int kn = (int)min(64l, K - k0);
         for (int kk = 0; kk < kn; ++kk) {
             const float xv = xs[ty][kk];
             acc_a = fmaf(xv, ws[0][tx][kk], acc_a);
@@ -243,92 +253,13 @@ __global__ __launch_bounds__(256) void mlp_f32_kernel(const float* __restrict__ 
     if constexpr (GATE) {
         float a = acc_a / (1.0f + expf(-acc_a));
         if (two) a *= acc_b;
-        out[(size_t)r * ldo + n] = a;
+        store_act(out, (size_t)r * ldo + n, a);   // an activation row: ldo elements (pairs)
     } else {
-        out[(size_t)r * ldo + n] = h[(size_t)state_of(r) * N + n] + acc_a;
+        store_elem(out, (size_t)r * ldo + n, load_elem(h, (size_t)state_of(r) * N + n) + acc_a);
     }
 }
 
 // ------------------------------------------------------------------ launcher
-
-// Epilogue makers: each product's epilogue for the (WM, NT) its plan picks.
-struct MakeStoreH {   // the h~ half: fp32 table, one row per drafter state
-    float* out;
-    int ldo;
-    template <int WM, int NT>
-    EpiStoreF32<WM, NT> make() const { return EpiStoreF32<WM, NT>{out, ldo}; }
-};
-struct MakeSwiGLUH {   // the e~ half of gate/up: + h~ half, SwiGLU
-    uint16_t* act;
-    int I;
-    const float* hh;
-    int ldh;
-    RowTable rt;
-    template <int WM, int NT>
-    EpiAddH<WM, NT, EpiSwiGLU<WM, NT>> make() const {
-        return EpiAddH<WM, NT, EpiSwiGLU<WM, NT>>{EpiSwiGLU<WM, NT>{act, I}, hh, ldh, rt};
-    }
-};
-struct MakeSiLUH {   // the e~ half of the plain SiLU gate
-    uint16_t* act;
-    int I;
-    const float* hh;
-    int ldh;
-    RowTable rt;
-    template <int WM, int NT>
-    EpiAddH<WM, NT, EpiSiLU<WM, NT>> make() const {
-        return EpiAddH<WM, NT, EpiSiLU<WM, NT>>{EpiSiLU<WM, NT>{act, I}, hh, ldh, rt};
-    }
-};
-struct MakeResidual {   // the down projection: + h
-    uint16_t* hp;
-    const uint16_t* h;
-    int d;
-    RowTable rt;
-    template <int WM, int NT>
-    EpiResidual<WM, NT> make() const { return EpiResidual<WM, NT>{hp, h, d, rt}; }
-};
-struct MakeResidualH {   // the e~ half of the linear layer: + h~ half, + h
-    uint16_t* hp;
-    const uint16_t* h;
-    int d;
-    RowTable rt;
-    const float* hh;
-    int ldh;
-    template <int WM, int NT>
-    EpiAddH<WM, NT, EpiResidual<WM, NT>> make() const {
-        return EpiAddH<WM, NT, EpiResidual<WM, NT>>{EpiResidual<WM, NT>{hp, h, d, rt}, hh, ldh, rt};
-    }
-};
-
-template <int WM, int NT, class WSrc, class XSrc, class Maker>
-static void run_product_nt(const GemmPlan& p, const WSrc& ws, const XSrc& xs, int rows, int K, const Maker& mk,
-                           float* partial, int* counters, hipStream_t st) {
-    constexpr int S = TF_NW_SINGLE, P = TF_PIPE_DEFAULT;
-    using Inner = decltype(mk.template make<WM, NT>());
-    const GemmShape sh = p.shape(rows, K);
-    if (p.NW != S) {
-        using E = EpiFixup<WM, NT, TF_NW, Inner>;
-        hipLaunchKernelGGL((product_bf16_kernel<WM, NT, TF_NW, P, false, WSrc, XSrc, E>), dim3(sh.G),
-                           dim3(64 * TF_NW), 0, st, ws, xs, sh, E{mk.template make<WM, NT>(), partial, counters});
-    } else {
-        using E = EpiFixup<WM, NT, S, Inner>;
-        hipLaunchKernelGGL((product_bf16_kernel<WM, NT, S, P, false, WSrc, XSrc, E>), dim3(sh.G), dim3(64 * S), 0,
-                           st, ws, xs, sh, E{mk.template make<WM, NT>(), partial, counters});
-    }
-}
-
-// One product with the tile shape its plan picks (plan_nt / plan_wm).
-template <class WSrc, class XSrc, class Maker>
-static void run_product(const GemmPlan& p, const WSrc& ws, const XSrc& xs, int rows, int K, const Maker& mk,
-                        float* partial, int* counters, hipStream_t st) {
-    if (p.NT == 1)
-        run_product_nt<2, 1>(p, ws, xs, rows, K, mk, partial, counters, st);
-    else if (p.NT == 2)
-        run_product_nt<1, 2>(p, ws, xs, rows, K, mk, partial, counters, st);
-    else
-        run_product_nt<1, 4>(p, ws, xs, rows, K, mk, partial, counters, st);
-}
 
 static bool aligned16p(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -420,6 +351,140 @@ static hipError_t launch_arapprox_dma(const void* h, const int32_t* root, const 
                                       void* et, void* act, void* hp, float* partial, int* counters, int* diag,
                                       hipStream_t stream);
 
+// One product with its finished outputs: from the accumulators, or from the
+// splits' tables.
+static hipError_t tile_product_finished(const TilePlan& p, bool paired, const uint16_t* wa, const uint16_t* wb,
+                                        const uint16_t* x, long ldx, int Kw, int K, float* tables, TileFinish f,
+                                        hipStream_t st) {
+    TileProductArgs a{};
+    a.seg[0] = TileSegment{wa, wb, x, f.R, tables};
+    a.nseg = 1;
+    a.gateup = wb != nullptr;
+    a.N = f.N;
+    a.Kw = Kw;
+    a.K = K;
+    a.ldx = ldx;
+    a.fin = f;
+    const hipError_t e = launch_tile_product(p, paired, a, st);
+    if (e != hipSuccess || p.S == 1) return e;
+    f.own = tables;
+    f.nown = p.S;
+    return launch_tile_finish(f, st);
+}
+
+// Eq. 1 on the block-tiled products: more rows than one row block, or widths
+// or states that the one-row-block kernels do not take.  The input projection
+// is split at the h~ / e~ boundary (the h~ half once per drafter state); the
+// bigram rows, which combine few distinct tokens in many pairs, have it split
+// once more, at the previous token's boundary, and computed once per token
+// (at 16 x 8 candidates 122 tokens for 905 rows, a seventh of the products).
+static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const int32_t* context,
+                                       const int32_t* topk_idx, const void* emb, const void* gain_h,
+                                       const void* gain_e, const void* w_gate, const void* w_up, const void* w_down,
+                                       int b, int d, int I, int V, const RowTable& rt, float eps, void* ht, void* et,
+                                       void* act, void* hp, float* partial, int* counters, float* hh, int* diag,
+                                       hipStream_t stream) {
+    const bool swiglu = w_up != nullptr;
+    const int rows = b * rt.Rs, states = b * rt.gamma;
+    const int N = swiglu ? 2 * I : I;
+    const uint16_t* hb = static_cast<const uint16_t*>(h);
+    const uint16_t* htb = static_cast<const uint16_t*>(ht);
+    const uint16_t* etb = static_cast<const uint16_t*>(et);
+    const uint16_t* wg = static_cast<const uint16_t*>(w_gate);
+    const uint16_t* wu = static_cast<const uint16_t*>(w_up);
+    uint16_t* actb = static_cast<uint16_t*>(act);
+    TileFinish f{};
+    f.epi = swiglu ? kTileSwiGLU : kTileSiLU;
+    f.R = rows;
+    f.N = N;
+    f.out = actb;
+    f.width = I;
+    f.hh = hh;
+    f.states = states;
+    f.rt = rt;
+    hipError_t e;
+    if (rt.bigram) {
+        const RowTable tt = make_token_table(rt.gamma, rt.M);
+        const int tokens = b * tt.Rs;
+        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, tt, 1, eps, ht, et, diag,
+                               counters, 0, stream);
+        float* t1 = hh + (size_t)states * N;
+        float* t2 = t1 + (size_t)tokens * N;
+        TileProductArgs a{};
+        a.seg[0] = TileSegment{wg, wu, htb, states, hh};
+        a.seg[1] = TileSegment{wg + d, wu + d, etb, tokens, t1};
+        a.seg[2] = TileSegment{wg + 2 * d, wu + 2 * d, etb, tokens, t2};
+        a.nseg = 3;
+        a.gateup = true;
+        a.N = N;
+        a.Kw = 3 * d;
+        a.K = d;
+        a.ldx = d;
+        e = launch_tile_product(tile_token_plan(tokens, N, d), false, a, stream);
+        if (e != hipSuccess) return e;
+        f.nhh = 1;
+        f.t1 = t1;
+        f.t2 = t2;
+        e = launch_tile_finish(f, stream);
+    } else if (mlp_dma_gate_applies(true, b, rt.gamma, rt.Rs, d, I, d)) {
+        // 129-256 rows of one or two sequences: the one-row-block kernel with eight activation tiles
+        const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, d, I, swiglu);
+        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
+                               counters, pg.items, stream);
+        const MlpDmaArgs ag = mlp_dma_args(pg, wg, wu, I, 2 * d, htb, etb, d, states, rows, actb, I, hb, rt, partial,
+                                           counters);
+        e = swiglu ? launch_mlp_dma<false, kMlpWGateUp, kMlpEpiSwiGLU>(ag, pg, stream)
+                   : launch_mlp_dma<false, kMlpWPlain, kMlpEpiSiLU>(ag, pg, stream);
+    } else {
+        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
+                               counters, 0, stream);
+        const TilePlan ph = tile_state_plan(states, N, d);
+        TileProductArgs a{};
+        a.seg[0] = TileSegment{wg, wu, htb, states, hh};
+        a.nseg = 1;
+        a.gateup = swiglu;
+        a.N = N;
+        a.Kw = 2 * d;
+        a.K = d;
+        a.ldx = d;
+        e = launch_tile_product(ph, false, a, stream);
+        if (e != hipSuccess) return e;
+        f.nhh = ph.S;
+        e = tile_product_finished(tile_input_plan(rows, N, d), false, wg + d, swiglu ? wu + d : nullptr, etb, d, 2 * d,
+                                  d, partial, f, stream);
+    }
+    if (e != hipSuccess) return e;
+    TileFinish r{};
+    r.epi = kTileResidual;
+    r.R = rows;
+    r.N = r.width = d;
+    r.out = static_cast<uint16_t*>(hp);
+    r.h = hb;
+    r.states = states;
+    r.rt = rt;
+    return tile_product_finished(tile_down_plan(rows, d, I), true, static_cast<const uint16_t*>(w_down), nullptr, actb,
+                                 2l * I, I, I, partial, r, stream);
+}
+
+template <class T>
+static hipError_t launch_arapprox_simt(const void* h, const int32_t* root, const int32_t* context,
+                                       const int32_t* topk_idx, const void* emb, const void* gain_h,
+                                       const void* gain_e, const void* w_gate, const void* w_up, const void* w_down,
+                                       int b, int d, int I, int V, const RowTable& rt, int npre, float eps, void* ht,
+                                       void* et, void* act, void* hp, int* diag, hipStream_t stream) {
+    const int rows = b * rt.Rs, ew = npre * d;
+    launch_norms<T>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag, nullptr, 0,
+                    stream);
+    hipLaunchKernelGGL((mlp_simt_kernel<T, true>), dim3(cdiv(I, 16), cdiv(rows, 16)), dim3(256), 0, stream,
+                       static_cast<const T*>(w_gate), static_cast<const T*>(w_up), I, (long)d + ew,
+                       static_cast<const T*>(ht), d, static_cast<const T*>(et), (long)ew, rt, rows, nullptr,
+                       static_cast<T*>(act), I);
+    hipLaunchKernelGGL((mlp_simt_kernel<T, false, true>), dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
+                       static_cast<const T*>(w_down), nullptr, d, (long)I, nullptr, 0, static_cast<const T*>(act),
+                       (long)I, rt, rows, static_cast<const T*>(h), static_cast<T*>(hp), d);
+    return hipGetLastError();
+}
+
 hipError_t launch_arapprox(const void* h, const int32_t* root, const int32_t* context, const int32_t* topk_idx,
                            const void* emb, const void* gain_h, const void* gain_e, const void* w_gate,
                            const void* w_up, const void* w_down, int b, int gamma, int d, int I, int V, int k,
@@ -433,70 +498,14 @@ hipError_t launch_arapprox(const void* h, const int32_t* root, const int32_t* co
         if (mlp_dma_applies(true, b, gamma, rt.Rs, d, I, ew))
             return launch_arapprox_dma(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d,
                                        I, V, rt, npre, eps, ht, et, act, hp, mlp_partial, counters, diag, stream);
-        if (mlp_dma_gate_applies(true, b, gamma, rt.Rs, d, I, ew)) {
-            // 129-256 rows: the input projections on the one-row-block kernel
-            // (eight activation tiles), the down projection over several row blocks
-            const bool swiglu = w_up != nullptr;
-            const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, ew, I, swiglu);
-            const GemmPlan pd = down_plan(rows, d, I);
-            launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et,
-                                   diag, counters, (int)(pg.items + pd.counter_ints()), stream);
-            const uint16_t* hb = static_cast<const uint16_t*>(h);
-            uint16_t* actb = static_cast<uint16_t*>(act);
-            const MlpDmaArgs ag = mlp_dma_args(pg, static_cast<const uint16_t*>(w_gate),
-                                               static_cast<const uint16_t*>(w_up), I, d + ew,
-                                               static_cast<const uint16_t*>(ht), static_cast<const uint16_t*>(et),
-                                               ew, b * rt.gamma, rows, actb, I, hb, rt, mlp_partial, counters);
-            const hipError_t e = swiglu ? launch_mlp_dma<false, kMlpWGateUp, kMlpEpiSwiGLU>(ag, pg, stream)
-                                        : launch_mlp_dma<false, kMlpWPlain, kMlpEpiSiLU>(ag, pg, stream);
-            if (e != hipSuccess) return e;
-            run_product(pd, WRowsPairedK{static_cast<const uint16_t*>(w_down), d, I}, XRowsPlain{actb, 2l * I},
-                        rows, 2 * I, MakeResidual{static_cast<uint16_t*>(hp), hb, d, rt}, mlp_partial,
-                        counters + pg.items, stream);
-            return hipGetLastError();
-        }
-        // several row blocks: the input projection split at the h~ / e~ boundary
-        // (the h~ half once per drafter state), then the down projection
-        const bool swiglu = w_up != nullptr;
-        const int states = b * rt.gamma;
-        const SplitPlans sp = split_plans(swiglu ? 0 : 1, states, rows, d, ew, I);
-        const GemmPlan pd = down_plan(rows, d, I);
-        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
-                               counters, (int)(sp.counter_ints() + pd.counter_ints()), stream);
-        const uint16_t* hb = static_cast<const uint16_t*>(h);
-        const uint16_t* wg = static_cast<const uint16_t*>(w_gate);
-        const uint16_t* wu = static_cast<const uint16_t*>(w_up);
-        const XRowsPlain xh{static_cast<const uint16_t*>(ht), d};
-        const XRowsPlain xe{static_cast<const uint16_t*>(et), ew};
-        uint16_t* actb = static_cast<uint16_t*>(act);
-        int* ce = counters + sp.ph.counter_ints();
-        int* cd = ce + sp.pe.counter_ints();
-        if (swiglu) {
-            run_product(sp.ph, WRowsGateUp{wg, wu, I, d + ew}, xh, states, d, MakeStoreH{hh, sp.ldh()}, mlp_partial,
-                        counters, stream);
-            run_product(sp.pe, WRowsGateUp{wg + d, wu + d, I, d + ew}, xe, rows, ew,
-                        MakeSwiGLUH{actb, I, hh, sp.ldh(), rt}, mlp_partial, ce, stream);
-        } else {
-            run_product(sp.ph, WRowsPlain{wg, I, d + ew}, xh, states, d, MakeStoreH{hh, sp.ldh()}, mlp_partial,
-                        counters, stream);
-            run_product(sp.pe, WRowsPlain{wg + d, I, d + ew}, xe, rows, ew, MakeSiLUH{actb, I, hh, sp.ldh(), rt},
-                        mlp_partial, ce, stream);
-        }
-        run_product(pd, WRowsPairedK{static_cast<const uint16_t*>(w_down), d, I}, XRowsPlain{actb, 2l * I}, rows,
-                    2 * I, MakeResidual{static_cast<uint16_t*>(hp), hb, d, rt}, mlp_partial, cd, stream);
-    } else {
-        launch_norms<float>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
-                            counters, 0, stream);
-        hipLaunchKernelGGL(mlp_f32_kernel<true>, dim3(cdiv(I, 16), cdiv(rows, 16)), dim3(256), 0, stream,
-                           static_cast<const float*>(w_gate), static_cast<const float*>(w_up), I, d + ew,
-                           static_cast<const float*>(ht), d, static_cast<const float*>(et), ew, rt, rows, nullptr,
-                           static_cast<float*>(act), I);
-        hipLaunchKernelGGL(mlp_f32_kernel<false>, dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
-                           static_cast<const float*>(w_down), nullptr, d, I, nullptr, 0,
-                           static_cast<const float*>(act), I, rt, rows, static_cast<const float*>(h),
-                           static_cast<float*>(hp), d);
+        if (tile_width_ok(d, ew, I))
+            return launch_arapprox_tile(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d,
+                                        I, V, rt, eps, ht, et, act, hp, mlp_partial, counters, hh, diag, stream);
+        return launch_arapprox_simt<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down,
+                                              b, d, I, V, rt, npre, eps, ht, et, act, hp, diag, stream);
     }
-    return hipGetLastError();
+    return launch_arapprox_simt<float>(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d, I,
+                                       V, rt, npre, eps, ht, et, act, hp, diag, stream);
 }
 
 hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int32_t* topk_idx, const void* emb,
@@ -517,26 +526,49 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
                                            counters);
         return launch_mlp_dma<false, kMlpWPlain, kMlpEpiResidual>(al, pl, stream);
     }
-    if (bf16) {
-        // several row blocks: the h~ half once per drafter state, then the e~ half with the residual
+    const bool tile = bf16 && tile_width_ok(d, d, d);
+    if (tile) {
+        // the h~ half once per drafter state, then the e~ half with the residual
         const int states = b * gamma;
-        const SplitPlans sp = split_plans(2, states, rows, d, d, d);
         launch_norms<uint16_t>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
-                               counters, (int)sp.counter_ints(), stream);
+                               counters, 0, stream);
         const uint16_t* wl = static_cast<const uint16_t*>(w_lin);
-        run_product(sp.ph, WRowsPlain{wl, d, 2 * d}, XRowsPlain{static_cast<const uint16_t*>(ht), d}, states, d,
-                    MakeStoreH{hh, sp.ldh()}, mlp_partial, counters, stream);
-        run_product(sp.pe, WRowsPlain{wl + d, d, 2 * d}, XRowsPlain{static_cast<const uint16_t*>(et), d}, rows, d,
-                    MakeResidualH{static_cast<uint16_t*>(hp), static_cast<const uint16_t*>(h), d, rt, hh, sp.ldh()},
-                    mlp_partial, counters + sp.ph.counter_ints(), stream);
-    } else {
-        launch_norms<float>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
-                            counters, 0, stream);
-        hipLaunchKernelGGL(mlp_f32_kernel<false>, dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
-                           static_cast<const float*>(w_lin), nullptr, d, 2 * d, static_cast<const float*>(ht), d,
-                           static_cast<const float*>(et), d, rt, rows, static_cast<const float*>(h),
-                           static_cast<float*>(hp), d);
+        TileProductArgs ah{};
+        ah.seg[0] = TileSegment{wl, nullptr, static_cast<const uint16_t*>(ht), states, hh};
+        ah.nseg = 1;
+        ah.N = d;
+        ah.Kw = 2 * d;
+        ah.K = d;
+        ah.ldx = d;
+        const TilePlan ph = tile_state_plan(states, d, d), pe = tile_input_plan(rows, d, d);
+        const hipError_t e = launch_tile_product(ph, false, ah, stream);
+        if (e != hipSuccess) return e;
+        TileFinish f{};
+        f.epi = kTileResidual;
+        f.R = rows;
+        f.N = f.width = d;
+        f.out = static_cast<uint16_t*>(hp);
+        f.h = static_cast<const uint16_t*>(h);
+        f.hh = hh;
+        f.nhh = ph.S;
+        f.states = states;
+        f.rt = rt;
+        return tile_product_finished(pe, false, wl + d, nullptr, static_cast<const uint16_t*>(et), d, 2 * d, d,
+                                     mlp_partial, f, stream);
     }
+    auto simt = [&](auto zero) {
+        using T = decltype(zero);
+        launch_norms<T>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag, counters, 0,
+                        stream);
+        hipLaunchKernelGGL((mlp_simt_kernel<T, false>), dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
+                           static_cast<const T*>(w_lin), nullptr, d, 2l * d, static_cast<const T*>(ht), d,
+                           static_cast<const T*>(et), (long)d, rt, rows, static_cast<const T*>(h),
+                           static_cast<T*>(hp), d);
+    };
+    if (bf16)
+        simt(uint16_t{});
+    else
+        simt(float{});
     return hipGetLastError();
 }
 

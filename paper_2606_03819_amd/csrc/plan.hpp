@@ -18,31 +18,10 @@ constexpr int kMaxTopk = 1024;         // longest top-k list the merge kernel so
 constexpr int kMaxBudget = 4095;       // tree nodes per sequence
 constexpr int kNumCUs = 256;           // compute units of an MI355X
 
-// Waves per workgroup of the bf16 streaming products with several row
-// blocks; one such workgroup fills a CU's register file at two waves per
-// SIMD.  A single row block uses half the waves (two workgroups per CU): the
-// k-range is cut there, and a smaller workgroup leaves the last piece's
-// workgroup less partial sum to read back.
-#ifndef TF_NW
-#define TF_NW 8
-#endif
-#ifndef TF_NW_SINGLE
-#define TF_NW_SINGLE 4
-#endif
 // Tile ranges (workgroups) of the LM head when a single row block streams
 // the whole vocabulary.
 #ifndef TF_LM_WORKGROUPS
 #define TF_LM_WORKGROUPS 256
-#endif
-// Workgroups of the SwiGLU gate/up and down products when a single row
-// block leaves too few weight tiles to occupy every CU (their k-range is
-// then cut; every cut adds a partial-sum round trip, so the smaller down
-// product uses fewer workgroups).
-#ifndef TF_MLP_WORKGROUPS
-#define TF_MLP_WORKGROUPS 512
-#endif
-#ifndef TF_DOWN_WORKGROUPS
-#define TF_DOWN_WORKGROUPS 256
 #endif
 // Pipeline depth (k-chunks of loads in flight per wave) when a single row
 // block streams the weights once at NT = 4, and otherwise; the launchers pick
@@ -56,61 +35,7 @@ constexpr int kNumCUs = 256;           // compute units of an MI355X
 
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-struct GemmPlan {
-    int NT;       // 32-row activation tiles per workgroup
-    int WM;       // 32-row weight tiles per wave (bf16)
-    int NW;       // waves per workgroup
-    int chunk;    // weight tiles per chunk (NW * WM)
-    int nrb;      // activation-row blocks
-    int ntiles;   // 32-row weight tiles
-    int nchunks;  // chunks (= vocabulary slices for the LM head)
-    int nk;       // 64-wide k-chunks
-    int G;        // workgroups
-    bool wnt;     // non-temporal weight loads (weights read by one row block only)
-    bool pieces;  // some item is cut between workgroups
-    int items() const { return nchunks * nrb; }
-    int blocks() const { return G; }
-    GemmShape shape(int R, int K) const { return GemmShape{R, K, ntiles, nchunks, nrb, nk, G}; }
-    // accumulators of one workgroup, in floats
-    size_t part_floats() const { return (size_t)NW * WM * NT * 16 * 64; }
-    // partial sums of cut items: two slots per workgroup
-    size_t fix_floats() const { return pieces ? 2 * (size_t)G * part_floats() : 0; }
-    size_t counter_ints() const { return pieces ? (size_t)items() : 0; }
-};
-
 inline int plan_nt(int rows) { return rows <= 32 ? 1 : (rows <= 64 ? 2 : 4); }
-// two weight tiles per wave at NT = 1; one otherwise keeps the accumulators,
-// the load pipeline and the epilogue within 256 registers
-inline int plan_wm(int NT) { return NT == 1 ? 2 : 1; }
-
-// bf16 product of `rows` activation rows with `ntiles` weight tiles over K.
-// Enough (chunk, row block) items of eight-wave workgroups to give every CU
-// one: one item per workgroup, the row blocks of a chunk on consecutive
-// workgroups so that they share the chunk through L2.  Fewer (one row block,
-// or a few): four-wave workgroups, the units cut evenly over `wg_single`
-// workgroups.
-inline GemmPlan gemm_plan(int rows, int ntiles, int K, int wg_single) {
-    GemmPlan p;
-    p.NT = plan_nt(rows);
-    p.WM = plan_wm(p.NT);
-    p.nrb = cdiv(rows, 32 * p.NT);
-    const bool whole = p.nrb > 1 && (long long)cdiv(ntiles, TF_NW * p.WM) * p.nrb >= kNumCUs;
-    p.NW = whole ? TF_NW : TF_NW_SINGLE;
-    p.chunk = p.NW * p.WM;
-    p.ntiles = ntiles;
-    p.nchunks = cdiv(ntiles, p.chunk);
-    p.nk = cdiv(K, 64);
-    if (!whole) {
-        const long long units = (long long)p.items() * p.nk;
-        p.G = (int)(units < wg_single ? units : wg_single);
-        if (p.G < p.items()) p.G = p.items();
-    } else {
-        p.G = p.items();
-    }
-    p.wnt = p.nrb == 1;
-    p.pieces = gemm_has_pieces(p.shape(rows, K));
-    return p;
-}
 
 // LM head over [rows, d] x [V, d]: vocabulary slices (see SliceMap), one
 // workgroup per (tile range, row block), the row blocks of a range on
@@ -275,39 +200,95 @@ inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
     return p;
 }
 
-// SwiGLU products (bf16).
-inline GemmPlan mlp_plan(int rows, int ntiles, int K, int wg_single) {
-    GemmPlan p = gemm_plan(rows, ntiles, K, wg_single);
-    p.wnt = false;   // every workgroup of a row block re-reads its weights from L2
-    return p;
-}
-// gate/up over x = [h~ ; e~], K = 2d (3d for the bigram rows)
-inline GemmPlan gateup_plan(int rows, int K, int I) { return mlp_plan(rows, cdiv(I, 16), K, TF_MLP_WORKGROUPS); }
-// the gate alone (plain SiLU MLP): tiles of 32 gate rows
-inline GemmPlan silu_gate_plan(int rows, int K, int I) { return mlp_plan(rows, cdiv(I, 32), K, TF_MLP_WORKGROUPS); }
-// down projection over the activation's bf16 hi/lo pairs: K = 2I
-inline GemmPlan down_plan(int rows, int d, int I) { return mlp_plan(rows, cdiv(d, 32), 2 * I, TF_DOWN_WORKGROUPS); }
-// the linear approximator: [rows, 2d] x [d, 2d]^T
-inline GemmPlan linear_plan(int rows, int d) { return mlp_plan(rows, cdiv(d, 32), 2 * d, TF_DOWN_WORKGROUPS); }
-// one half (h~ or e~) of the linear layer's input: [rows, d] x [d, d]^T
-inline GemmPlan linear_half_plan(int rows, int d) { return mlp_plan(rows, cdiv(d, 32), d, TF_DOWN_WORKGROUPS); }
-
-// The input projections over several activation row blocks, split at the
-// h~ / e~ boundary of x (Eq. 1): the h~ half once per drafter state
-// ([b*gamma, d] into an fp32 table of ldh() columns), the e~ half for every
-// row (K = ew), whose epilogue adds its state's entry of the table.
-struct SplitPlans {
-    GemmPlan ph, pe;
-    int ldh() const { return ph.ntiles * 32; }
-    size_t fix_floats() const { return ph.fix_floats() > pe.fix_floats() ? ph.fix_floats() : pe.fix_floats(); }
-    size_t counter_ints() const { return ph.counter_ints() + pe.counter_ints(); }
+// The approximator's products on the block-tiled GEMM (tile_product.hip): tiles
+// of 32 WMT weight rows x 32 NXT activation rows, the reduction range cut into
+// S splits of `per` 64-wide steps where there are fewer tiles than CUs.
+struct TilePlan {
+    int WMT, NXT;
+    int nrb, ntw;      // row blocks, weight tiles
+    int S, per, nk;    // splits, steps of a split, steps in all
+    double us;         // the model's time
+    int items() const { return nrb * ntw * S; }
 };
-// kind 0: SwiGLU gate/up, 1: the plain SiLU gate, 2: the linear layer
-inline SplitPlans split_plans(int kind, int states, int rows, int d, int ew, int I) {
-    if (kind == 0) return SplitPlans{gateup_plan(states, d, I), gateup_plan(rows, ew, I)};
-    if (kind == 1) return SplitPlans{silu_gate_plan(states, d, I), silu_gate_plan(rows, ew, I)};
-    return SplitPlans{linear_half_plan(states, d), linear_half_plan(rows, d)};
+
+// Tile shapes (WMT, NXT, activation pairs).
+#define TF_TILE_SHAPES(F)                                                                                     \
+    F(8, 8, false) F(6, 8, false) F(5, 8, false) F(4, 8, false) F(4, 4, false) F(2, 4, false) F(4, 2, false) \
+    F(8, 4, true) F(4, 4, true) F(2, 4, true) F(4, 2, true)
+
+constexpr int kTileSplits = 8;             // most splits
+constexpr int kTileSplitFloats = 16384;    // most fp32 partial sums of a row, over its splits
+constexpr int kTileSplitRows = 2048;       // rows up to which products are split (more rows make tiles enough)
+constexpr int kTileMinSteps = 4;           // fewest steps of a split
+
+// Partial sums a row's split products may take (floats): grows with N.
+inline long long tile_split_floats(int rows, long long N) {
+    if (rows > kTileSplitRows) return 0;
+    return N * kTileSplits < kTileSplitFloats ? N * kTileSplits : kTileSplitFloats;
 }
+
+// The shape and split that a simple time model finds fastest.  A step takes
+// what its MFMAs take at two thirds of the issue rate at 2.1 GHz (what the
+// 256 x 256 tile reaches under the card's power limit), or its copies into LDS
+// at 55 GB/s a CU (40 where fewer than four row blocks share a weight tile,
+// which then comes from HBM for most of them; 64 for activation pairs, whose
+// rows are 256 bytes a step); weights come from HBM at most at 25 GB/s a CU; a split's sums are
+// written and read back, and cost a launch.  Measured against the model
+// (us, 256 CUs): 1936 x 8192 x 4096 256 x 256 106 / 97, 128 x 256 119 / 120,
+// 160 x 256 130 / 130; 455 x 19456 x 2560 160 x 256 55 / 55, 192 x 256 59 / 59, 256 x 256 72 / 67;
+// 256 x 8192 x 4096 128 x 128 in two splits 30 / 30, 64 x 128 33 / 41; pairs:
+// 905 x 4096 x 4096 128 x 128 56 / 51, 256 x 128 in two splits 60 / 62.
+inline TilePlan tile_plan(int rows, int N, int K, int nseg, bool paired, int max_splits, bool tables) {
+    TilePlan best{};
+    best.us = 1e30;
+    const int np = paired ? 2 : 1;
+    const int nk = cdiv(K, 64);
+    const double wbytes = 2.0 * N * K * nseg;
+    auto consider = [&](int WMT, int NXT) {
+        TilePlan p;
+        p.WMT = WMT;
+        p.NXT = NXT;
+        p.nk = nk;
+        p.nrb = cdiv(rows, 32 * NXT);
+        p.ntw = cdiv(N, 32 * WMT);
+        const double copy = 32.0 * (WMT + NXT * np) * 128 / (paired ? 64e3 : (p.nrb >= 4 ? 55e3 : 40e3));
+        const double mfma = 32.0 * WMT * NXT * np * 1.5 / 2100;
+        const double step = copy > mfma ? copy : mfma;
+        for (int S = 1; S <= max_splits; S += S < 4 ? 1 : 2) {
+            if (S > 1 && (nk < S * kTileMinSteps || (long long)S * N > tile_split_floats(rows, N))) break;
+            p.per = cdiv(nk, S);
+            p.S = cdiv(nk, p.per);
+            const long long items = (long long)p.items() * nseg;
+            const double rounds = (double)cdiv(items, kNumCUs);
+            double us = rounds * (p.per * step + 3);
+            const double hbm = wbytes / ((items < kNumCUs ? items : kNumCUs) * 25e3) + 4;
+            if (hbm > us) us = hbm;
+            if (p.S > 1) us += tables ? 4.0 * p.S * rows * N / 8e6 : 4 + 8.0 * p.S * rows * N / 8e6;
+            p.us = us;
+            if (us < best.us) best = p;
+        }
+    };
+#define TF_TILE_CONSIDER(W, X, P) \
+    if (paired == P) consider(W, X);
+    TF_TILE_SHAPES(TF_TILE_CONSIDER)
+#undef TF_TILE_CONSIDER
+    return best;
+}
+
+// Widest reduction or activation row whose byte offsets within a tile stay
+// below kTileSpan; wider ones (weights of more than 2^20 columns, and so of
+// few rows) take a plain kernel.
+inline bool tile_width_ok(int d, int ew, int I) { return d <= kTileMaxK - ew && I <= kTileMaxK; }
+
+// The h~ half of an input projection ([states, d] into fp32 tables of N
+// columns, the readers add its splits), the e~ half, the down projection.
+inline TilePlan tile_state_plan(int states, int N, int d) { return tile_plan(states, N, d, 1, false, 2, true); }
+inline TilePlan tile_input_plan(int rows, int N, int ew) {
+    return tile_plan(rows, N, ew, 1, false, kTileSplits, false);
+}
+inline TilePlan tile_down_plan(int rows, int d, int I) { return tile_plan(rows, d, I, 1, true, kTileSplits, false); }
+// the bigram rows' products, once per state and previous token
+inline TilePlan tile_token_plan(int tokens, int N, int d) { return tile_plan(tokens, N, d, 3, false, 1, true); }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -433,6 +414,9 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
     const size_t es = bf16 ? 2 : 4;
     const int rows1 = b * gamma, rows2 = b * R;
     const size_t lm1 = lm_scratch_bytes(rows1, V, d, bf16), lm2 = lm_scratch_bytes(rows2, V, d, bf16);
+    const bool tables = bf16 && bigram && !mlp_dma_applies(true, b, gamma, R, d, I, npre * d) &&
+                        tile_width_ok(d, npre * d, I);
+    const size_t tokens = (size_t)b * bigram_tokens(gamma, k);
     Workspace w;
     size_t off = 0;
     w.diag = off;
@@ -442,7 +426,7 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
     w.ht = off;
     off += align256((size_t)rows1 * d * es);
     w.et = off;
-    off += align256((size_t)rows2 * npre * d * es);
+    off += align256((tables ? tokens : (size_t)rows2 * npre) * d * es);
     w.act = off;
     off += align256((size_t)rows2 * I * es * (bf16 ? 2 : 1));   // bf16: hi/lo pairs
     w.hp = off;
@@ -451,37 +435,35 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
     w.ncounters = 0;
     size_t hhf = 0;
     if (bf16) {
-        const SplitPlans sg = split_plans(0, rows1, rows2, d, npre * d, I), ss = split_plans(1, rows1, rows2, d, npre * d, I),
-                         sl = split_plans(2, rows1, rows2, d, d, I);
-        const GemmPlan pd = down_plan(rows2, d, I);
-        const size_t fx[] = {sg.fix_floats(), ss.fix_floats(), sl.fix_floats(), pd.fix_floats()};
-        for (size_t x : fx) mp = mp > x ? mp : x;
-        size_t nc = sg.counter_ints() + pd.counter_ints();
-        nc = nc > ss.counter_ints() + pd.counter_ints() ? nc : ss.counter_ints() + pd.counter_ints();
-        nc = nc > sl.counter_ints() ? nc : sl.counter_ints();
-        const int ldh[] = {sg.ldh(), ss.ldh(), sl.ldh()};
-        for (int x : ldh) hhf = hhf > (size_t)rows1 * x ? hhf : (size_t)rows1 * x;
+        // The linear layer asks for this layout at the smallest I, whatever
+        // I the workspace was sized with: its needs are part of every layout,
+        // and no term shrinks as I grows.
+        const long long gf = tile_split_floats(rows2, 2ll * I), df = tile_split_floats(rows2, d);
+        mp = (size_t)rows2 * (gf > df ? gf : df);
+        const size_t ld = 2 * (size_t)I > (size_t)d ? 2 * (size_t)I : (size_t)d;
+        hhf = (size_t)rows1 * ld * (rows1 <= kTileSplitRows ? 2 : 1) + (tables ? 2 * tokens * ld : 0);
+        size_t nc = 0;
+        if (mlp_dma_applies(bf16, b, gamma, R, d, 64, d)) {
+            const MlpDmaPlan ql = mlp_dma_linear_plan(rows2, d);
+            mp = mp > ql.part_floats() ? mp : ql.part_floats();
+            nc = ql.items;
+        }
         if (mlp_dma_applies(bf16, b, gamma, R, d, I, npre * d)) {
             // either the SwiGLU or the SiLU gate plan (the SwiGLU one has more
-            // items), the down projection, the linear approximator
+            // items), and the down projection
             const MlpDmaPlan qg = mlp_dma_gate_plan(rows2, d, npre * d, I, true),
-                             qs = mlp_dma_gate_plan(rows2, d, npre * d, I, false), qd = mlp_dma_down_plan(rows2, d, I),
-                             ql = mlp_dma_linear_plan(rows2, d);
-            const size_t pf[] = {qg.part_floats(), qs.part_floats(), qd.part_floats(), ql.part_floats()};
+                             qs = mlp_dma_gate_plan(rows2, d, npre * d, I, false), qd = mlp_dma_down_plan(rows2, d, I);
+            const size_t pf[] = {qg.part_floats(), qs.part_floats(), qd.part_floats()};
             for (size_t x : pf) mp = mp > x ? mp : x;
             const size_t qc = (size_t)qg.items + qd.items;
             nc = nc > qc ? nc : qc;
-            nc = nc > (size_t)ql.items ? nc : (size_t)ql.items;
         }
-        if (mlp_dma_gate_applies(bf16, b, gamma, R, d, I, npre * d)) {
-            // either gate plan on the one-row-block kernel, then the down
-            // projection of several row blocks
-            const MlpDmaPlan qg = mlp_dma_gate_plan(rows2, d, npre * d, I, true),
-                             qs = mlp_dma_gate_plan(rows2, d, npre * d, I, false);
+        if (!bigram && mlp_dma_gate_applies(bf16, b, gamma, R, d, I, d)) {
+            // either gate plan on the one-row-block kernel
+            const MlpDmaPlan qg = mlp_dma_gate_plan(rows2, d, d, I, true), qs = mlp_dma_gate_plan(rows2, d, d, I, false);
             mp = mp > qg.part_floats() ? mp : qg.part_floats();
             mp = mp > qs.part_floats() ? mp : qs.part_floats();
-            const size_t qc = (size_t)qg.items + pd.counter_ints();
-            nc = nc > qc ? nc : qc;
+            nc = nc > (size_t)qg.items ? nc : (size_t)qg.items;
         }
         w.ncounters = (int)nc;
     }

@@ -1,8 +1,7 @@
 // Weight-streaming GEMM for gfx950: Y[r, n] = sum_k X[r, k] * W[n, k].
 //
-// Every product on the drafting path has this shape: a large weight matrix
-// (LM head [V, d], SwiGLU gate/up [I, 2d], down [d, I]) streamed once from HBM
-// against a small set of activation rows (b*gamma or b*R rows).  The weight
+// The LM head of at most 128 rows: a large weight matrix [V, d] streamed once
+// from HBM against a small set of activation rows.  The weight
 // side is the MFMA "A" operand (32 weight rows per tile), the activation rows
 // the "B" operand (32 rows per N-tile).  Each lane of a 32x32 accumulator then
 // owns one activation row (lane % 32) and 16 weight rows, so per-row
@@ -12,7 +11,7 @@
 // Work decomposition (see work.hpp): a workgroup of NW waves streams chunks
 // of NW*WM weight tiles (WM per wave) against blocks of 32*NT activation rows.
 // The LM head cuts the vocabulary into equal tile ranges, one per workgroup,
-// streamed in rounds; the small SwiGLU products cut their k-range instead.
+// streamed in rounds.
 // Per 64-wide k-chunk the activation tile [32*NT x 64] is staged in LDS
 // (double buffered, rows padded to 144 B so the 16-byte fragment reads are
 // bank-conflict free) and shared by all NW*WM weight tiles of the workgroup.
@@ -32,7 +31,6 @@
 #pragma once
 
 #include "common.hpp"
-#include "rows.hpp"
 #include "work.hpp"
 
 namespace tf {
@@ -44,14 +42,11 @@ struct Segment {
     int t0, t1;    // weight tiles [t0, t1)
     int kc0, kc1;  // 64-wide k-chunks [kc0, kc1)
     int row0;      // first activation row
-    int gfirst;    // first workgroup holding a piece of the item
-    int npieces;   // workgroups holding a piece of the item
 };
 
 // Workgroups are dispatched round-robin over the 8 XCDs of an MI355X.
 // Renumber them so consecutive logical ids share an XCD (and its L2): the
-// row blocks of one weight chunk, and the pieces of a cut item, then meet in
-// the same L2.
+// row blocks of one weight chunk then meet in the same L2.
 __device__ __forceinline__ int xcd_logical_id(int bid, int nblocks) {
     if ((nblocks & 7) != 0) return bid;
     return (bid & 7) * (nblocks >> 3) + (bid >> 3);
@@ -68,32 +63,10 @@ struct GemmTraits {
     static constexpr int WS_BYTES = NW * WROWS * KC * 2;   // wave-private weight tiles
     static constexpr int SMEM_BYTES = XS_BYTES + WS_BYTES;
     static constexpr int NWL = WROWS / 8;        // coalesced weight loads per wave per k-chunk
-    static constexpr int CHUNK = NW * WM;        // weight tiles per chunk
     static constexpr int NTHREADS = 64 * NW;
     static constexpr int XPIECES = TR * 8;       // 16-byte pieces of an activation tile
     static constexpr int XPT = (XPIECES + NTHREADS - 1) / NTHREADS;
-    static constexpr int PART_FLOATS = NW * WM * NT * 16 * 64;   // one workgroup's accumulators
 };
-
-// The segment of workgroup g that starts at unit u (u < end of g's range).
-template <int WM, int NT, int NW>
-__device__ __forceinline__ Segment make_segment(const GemmShape& sh, int g, long long u, long long u_end) {
-    using T = GemmTraits<WM, NT, NW>;
-    Segment s;
-    s.g = g;
-    s.item = (int)(u / sh.nk);
-    s.chunk = s.item / sh.nrb;
-    s.rb = s.item - s.chunk * sh.nrb;
-    const long long ib = (long long)s.item * sh.nk;
-    s.kc0 = (int)(u - ib);
-    s.kc1 = (int)((u_end - ib) < sh.nk ? (u_end - ib) : sh.nk);
-    s.t0 = s.chunk * T::CHUNK;
-    s.t1 = min(s.t0 + T::CHUNK, sh.ntiles);
-    s.row0 = s.rb * T::TR;
-    s.gfirst = unit_owner(sh, ib);
-    s.npieces = unit_owner(sh, ib + sh.nk - 1) - s.gfirst + 1;
-    return s;
-}
 
 __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
 
@@ -285,25 +258,6 @@ __device__ __forceinline__ void gemm_segment(const WSrc& wsrc, const XSrc& xsrc,
     }
 }
 
-// Every segment of this workgroup: accumulate, then hand the accumulators to
-// the epilogue (which may reuse the LDS tiles).
-template <int WM, int NT, int NW, int PIPE, bool WNT, class WSrc, class XSrc, class Epi>
-__device__ __forceinline__ void stream_gemm(const WSrc& wsrc, const XSrc& xsrc, Epi& epi, const GemmShape& sh,
-                                            unsigned char* smem) {
-    const int g = xcd_logical_id(blockIdx.x, gridDim.x);
-    const long long u_end = unit_start(sh, g + 1);
-    long long u = unit_start(sh, g);
-    while (u < u_end) {
-        const Segment seg = make_segment<WM, NT, NW>(sh, g, u, u_end);
-        f32x16 acc[WM][NT];
-        gemm_segment<WM, NT, NW, PIPE, WNT>(wsrc, xsrc, sh, seg, acc, smem);
-        __syncthreads();  // LDS tiles no longer needed
-        epi.apply(acc, seg, smem, sh);
-        u = (long long)(seg.item + 1) * sh.nk;
-        if (u < u_end) lds_barrier();  // the epilogue's LDS use ends before the next tiles land
-    }
-}
-
 // ----------------------------------------------------------- weight sources
 
 // Plain [N, K] weight matrix, one weight row per tile row.
@@ -317,59 +271,12 @@ struct WRowsPlain {
     __device__ __forceinline__ int kcol(int k) const { return k; }
 };
 
-// Weight rows [N, K] read against an activation stored as bf16 hi/lo pairs
-// interleaved by 8 (activation column k' holds the hi part of element
-// (k'/16)*8 + k'%8 when (k'/8) is even, the lo part when odd): reduction
-// column k' reads weight column kcol(k').  The two lanes that load the hi
-// and lo columns of the same 8 weights read the same 16 bytes, so the weight
-// bytes fetched do not change.
-struct WRowsPairedK {
-    const uint16_t* w;
-    int N, K;   // K: weight columns (half the activation width)
-    __device__ __forceinline__ const uint16_t* row(int tile, int r) const {
-        const int n = tile * 32 + r;
-        return n < N ? w + (size_t)n * K : nullptr;
-    }
-    __device__ __forceinline__ int kcol(int k) const { return ((k >> 4) << 3) | (k & 7); }
-};
-
-// SwiGLU input projections: tile rows 0..15 are gate rows 16*tile.., tile
-// rows 16..31 the up rows with the same indices, so lane j of the accumulator
-// holds a gate value in register j and the matching up value in register j+8.
-struct WRowsGateUp {
-    const uint16_t* gate;
-    const uint16_t* up;
-    int I, K;
-    __device__ __forceinline__ const uint16_t* row(int tile, int r) const {
-        const int i = tile * 16 + (r & 15);
-        if (i >= I) return nullptr;
-        return (r < 16 ? gate : up) + (size_t)i * K;
-    }
-    __device__ __forceinline__ int kcol(int k) const { return k; }
-};
-
 // -------------------------------------------------------- activation sources
 
 struct XRowsPlain {
     const uint16_t* x;
     long ld;
     __device__ __forceinline__ const uint16_t* ptr(int r, int k) const { return x + (size_t)r * ld + k; }
-};
-
-// Input of the SwiGLU (or linear layer): row r is [ h~(depth of r) ; e~(r) ]
-// (Eq. 1), where e~(r) holds the normalised embeddings of the row's previous
-// token(s): ew = d for one token, 2d for the bigram of the w/ 2-prev rows.
-struct XRowsConcat {
-    const uint16_t* ht;   // [b*gamma, d] normalised drafter states
-    const uint16_t* et;   // [b*R, ew] normalised embeddings of the previous tokens
-    int d, ew;
-    RowTable t;
-    __device__ __forceinline__ const uint16_t* ptr(int r, int k) const {
-        if (k >= d) return et + (size_t)r * ew + (k - d);
-        const int s = r / t.Rs;
-        const int rl = r - s * t.Rs;
-        return ht + (size_t)(s * t.gamma + t.depth(rl) - 1) * d + k;
-    }
 };
 
 // ------------------------------------------------------------------ epilogues
@@ -636,294 +543,11 @@ struct EpiLmHead {
     }
 };
 
-// Cut items: every workgroup holding a piece stores its accumulators, and
-// the last one to arrive sums the pieces in workgroup order (so the result
-// does not depend on arrival order) and runs the real epilogue.  The arrival
-// counters are zeroed before the product starts.
-//
-// The pieces may sit on different XCDs, whose L2 caches are not coherent
-// with each other.  A device-scope fence would write back and invalidate the
-// whole L2 of the XCD (stalling every workgroup there), so only this
-// traffic is made device-coherent: the partial sums are written and read with
-// device-scope relaxed atomics (write-through stores and loads that do not
-// hit stale lines), the writer waits for its stores to complete before it
-// bumps the counter, and the reader loads only after seeing the count.
-__device__ __forceinline__ void store_coherent(float* p, float v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float load_coherent(const float* p) {
-    return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // every memory operation of this thread issued so far has completed
 __device__ __forceinline__ void wait_memory() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
-
-template <int WM, int NT, int NW, class Inner>
-struct EpiFixup {
-    Inner inner;
-    float* partial;   // [2 * G][PART_FLOATS]
-    int* counter;     // [items]
-
-    __device__ __forceinline__ void apply(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char* smem,
-                                          const GemmShape& sh) {
-        if (it.npieces > 1 && !combine(acc, it, smem, sh)) return;
-        inner.apply(acc, it, smem, sh);
-    }
-
-    // Store this piece; if it is the last to arrive, replace acc by the sum
-    // of all pieces and return true.
-    __device__ __forceinline__ bool combine(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char* smem,
-                                         const GemmShape& sh) {
-        constexpr int PF = GemmTraits<WM, NT, NW>::PART_FLOATS;
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-        // register j of accumulator (mt, nt) of all 64 lanes: one 256-byte row
-        auto idx = [&](int mt, int nt, int j) { return (((wave * WM + mt) * NT + nt) * 16 + j) * 64 + lane; };
-        float* mine = partial + (size_t)piece_slot(sh, it.g, it.item) * PF;
-#pragma unroll
-        for (int mt = 0; mt < WM; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) store_coherent(mine + idx(mt, nt, j), acc[mt][nt][j]);
-        wait_memory();
-        __syncthreads();   // every thread's piece is stored
-        int* flag = reinterpret_cast<int*>(smem);
-        if (threadIdx.x == 0)
-            flag[0] = (__hip_atomic_fetch_add(counter + it.item, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                       it.npieces - 1)
-                          ? 1
-                          : 0;
-        __syncthreads();
-        const bool last = flag[0] != 0;
-        __syncthreads();   // flag read by all before the epilogue reuses the LDS
-        if (!last) return false;
-        // pieces in workgroup order (this workgroup's own one re-read from
-        // memory, so every sum is the same chain of additions); the loads of
-        // one piece are independent, so each piece costs one round trip
-#pragma unroll
-        for (int mt = 0; mt < WM; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) acc[mt][nt][j] = 0.f;
-        for (int pc = 0; pc < it.npieces; ++pc) {
-            const float* src = partial + (size_t)piece_slot(sh, it.gfirst + pc, it.item) * PF;
-            f32x16 v[WM][NT];
-#pragma unroll
-            for (int mt = 0; mt < WM; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) v[mt][nt][j] = load_coherent(src + idx(mt, nt, j));
-#pragma unroll
-            for (int mt = 0; mt < WM; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) acc[mt][nt][j] += v[mt][nt][j];
-        }
-        return true;
-    }
-};
-
-// SwiGLU activation: a[r, i] = bf16( silu(g) * u ).
-template <int WM, int NT>
-struct EpiSwiGLU {
-    // [R, 2I]: a = silu(g) * u as bf16 pairs, hi = bf16(a), lo = bf16(a - hi),
-    // interleaved by 8 (hi of elements 8j..8j+7, then their lo), so the down
-    // projection reads the activation at about 16 significant bits
-    uint16_t* out;
-    int I;
-    __device__ __forceinline__ void apply(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char*,
-                                          const GemmShape& sh) {
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int mt = 0; mt < WM; ++mt) {
-            const int tile = it.t0 + wave * WM + mt;
-            if (tile >= it.t1) continue;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int r = it.row0 + nt * 32 + (lane & 31);
-                if (r >= sh.R) continue;
-#pragma unroll
-                for (int jg = 0; jg < 2; ++jg) {
-                    const int i = tile * 16 + 8 * jg + 4 * (lane >> 5);
-                    if (i >= I) continue;
-                    uint32_t hi2[2], lo2[2];
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        float a[2];
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const float g = acc[mt][nt][4 * jg + 2 * q + e];
-                            const float u = acc[mt][nt][4 * jg + 2 * q + e + 8];
-                            // silu(g) = g / (1 + e^-g), the quotient by the hardware reciprocal
-                            a[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-                        }
-                        hi2[q] = f32x2_to_bf16x2_bits(a[0], a[1]);
-                        lo2[q] = f32x2_to_bf16x2_bits(a[0] - bf16_bits_to_f32(hi2[q] & 0xffffu),
-                                                      a[1] - bf16_bits_to_f32(hi2[q] >> 16));
-                    }
-                    uint16_t* o = out + (size_t)r * 2 * I + (size_t)(i >> 3) * 16 + (i & 7);
-                    *reinterpret_cast<uint2*>(o) = uint2{hi2[0], hi2[1]};
-                    *reinterpret_cast<uint2*>(o + 8) = uint2{lo2[0], lo2[1]};
-                }
-            }
-        }
-    }
-};
-
-// Plain SiLU activation (no up projection): a[r, i] = silu(g) for tiles of
-// 32 gate rows, written as bf16 hi/lo pairs interleaved by 8 like EpiSwiGLU.
-template <int WM, int NT>
-struct EpiSiLU {
-    uint16_t* out;   // [R, 2I]
-    int I;
-    __device__ __forceinline__ void apply(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char*,
-                                          const GemmShape& sh) {
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int mt = 0; mt < WM; ++mt) {
-            const int tile = it.t0 + wave * WM + mt;
-            if (tile >= it.t1) continue;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int r = it.row0 + nt * 32 + (lane & 31);
-                if (r >= sh.R) continue;
-#pragma unroll
-                for (int jg = 0; jg < 4; ++jg) {
-                    const int i = tile * 32 + 8 * jg + 4 * (lane >> 5);
-                    if (i >= I) continue;
-                    uint32_t hi2[2], lo2[2];
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        float a[2];
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const float g = acc[mt][nt][4 * jg + 2 * q + e];
-                            a[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
-                        }
-                        hi2[q] = f32x2_to_bf16x2_bits(a[0], a[1]);
-                        lo2[q] = f32x2_to_bf16x2_bits(a[0] - bf16_bits_to_f32(hi2[q] & 0xffffu),
-                                                      a[1] - bf16_bits_to_f32(hi2[q] >> 16));
-                    }
-                    uint16_t* o = out + (size_t)r * 2 * I + (size_t)(i >> 3) * 16 + (i & 7);
-                    *reinterpret_cast<uint2*>(o) = uint2{hi2[0], hi2[1]};
-                    *reinterpret_cast<uint2*>(o + 8) = uint2{lo2[0], lo2[1]};
-                }
-            }
-        }
-    }
-};
-
-// fp32 store of the product: out[r, tile*32 + row of the tile] (the h~
-// half of an input projection, one row per drafter state).
-template <int WM, int NT>
-struct EpiStoreF32 {
-    float* out;
-    int ldo;
-    __device__ __forceinline__ void apply(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char*,
-                                          const GemmShape& sh) {
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int mt = 0; mt < WM; ++mt) {
-            const int tile = it.t0 + wave * WM + mt;
-            if (tile >= it.t1) continue;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int r = it.row0 + nt * 32 + (lane & 31);
-                if (r >= sh.R) continue;
-#pragma unroll
-                for (int jg = 0; jg < 4; ++jg) {
-                    const int n = tile * 32 + 8 * jg + 4 * (lane >> 5);
-                    *reinterpret_cast<f32x4*>(out + (size_t)r * ldo + n) =
-                        f32x4{acc[mt][nt][4 * jg], acc[mt][nt][4 * jg + 1], acc[mt][nt][4 * jg + 2],
-                              acc[mt][nt][4 * jg + 3]};
-                }
-            }
-        }
-    }
-};
-
-// Adds to every row's product the h~-half product of its drafter state
-// (EpiStoreF32's layout, the same weight tiles), then runs `inner`: the
-// product over x = [h~ ; e~] (Eq. 1) with the h~ half computed once per
-// (sequence, depth).
-template <int WM, int NT, class Inner>
-struct EpiAddH {
-    Inner inner;
-    const float* H;   // [b*gamma, ldh]
-    int ldh;
-    RowTable t;
-    __device__ __forceinline__ void apply(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char* smem,
-                                          const GemmShape& sh) {
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int r = it.row0 + nt * 32 + (lane & 31);
-            if (r >= sh.R) continue;
-            const int s = r / t.Rs;
-            const float* hrow = H + (size_t)(s * t.gamma + t.depth(r - s * t.Rs) - 1) * ldh;
-#pragma unroll
-            for (int mt = 0; mt < WM; ++mt) {
-                const int tile = it.t0 + wave * WM + mt;
-                if (tile >= it.t1) continue;
-#pragma unroll
-                for (int jg = 0; jg < 4; ++jg) {
-                    const f32x4 hv = *reinterpret_cast<const f32x4*>(hrow + tile * 32 + 8 * jg + 4 * (lane >> 5));
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[mt][nt][4 * jg + q] += hv[q];
-                }
-            }
-        }
-        inner.apply(acc, it, smem, sh);
-    }
-};
-
-// Residual: h'[r, n] = bf16( h[seq, depth-1, n] + y[r, n] ).
-template <int WM, int NT>
-struct EpiResidual {
-    uint16_t* out;        // [R, d]
-    const uint16_t* h;    // [b, gamma, d]
-    int d;
-    RowTable t;
-    __device__ __forceinline__ void apply(f32x16 (&acc)[WM][NT], const Segment& it, unsigned char*,
-                                          const GemmShape& sh) {
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int r = it.row0 + nt * 32 + (lane & 31);
-            if (r >= sh.R) continue;
-            const int s = r / t.Rs;
-            const int rl = r - s * t.Rs;
-            const uint16_t* hrow = h + (size_t)(s * t.gamma + t.depth(rl) - 1) * d;
-#pragma unroll
-            for (int mt = 0; mt < WM; ++mt) {
-                const int tile = it.t0 + wave * WM + mt;
-                if (tile >= it.t1) continue;
-#pragma unroll
-                for (int jg = 0; jg < 4; ++jg) {
-                    const int n = tile * 32 + 8 * jg + 4 * (lane >> 5);
-                    if (n >= d) continue;
-                    const uint2 hv = *reinterpret_cast<const uint2*>(hrow + n);
-                    const float h0 = bf16_bits_to_f32(hv.x & 0xffffu), h1 = bf16_bits_to_f32(hv.x >> 16);
-                    const float h2 = bf16_bits_to_f32(hv.y & 0xffffu), h3 = bf16_bits_to_f32(hv.y >> 16);
-                    const uint32_t o01 = f32x2_to_bf16x2_bits(h0 + acc[mt][nt][4 * jg + 0], h1 + acc[mt][nt][4 * jg + 1]);
-                    const uint32_t o23 = f32x2_to_bf16x2_bits(h2 + acc[mt][nt][4 * jg + 2], h3 + acc[mt][nt][4 * jg + 3]);
-                    *reinterpret_cast<uint2*>(out + (size_t)r * d + n) = uint2{o01, o23};
-                }
-            }
-        }
-    }
-};
 
 }  // namespace tf

@@ -26,8 +26,10 @@
 // step is a scalar offset (no address arithmetic in the loop, 1.5% faster
 // than 64-bit addresses), and rows past the operand's end read as zeros
 // without touching memory.  Weights go through a ring of three stages (copied
-// two steps ahead), activations through two; 16-byte slots are XOR-swizzled
-// by row so that the 16 rows a quarter-wave reads cover all 64 banks.
+// two steps ahead), activations through two; DEEP: four and three where the
+// LDS holds them, for tiles whose steps are shorter than a copy's latency.
+// 16-byte slots are XOR-swizzled by row so that the 16 rows a quarter-wave
+// reads cover all 64 banks.
 //
 // One barrier a step, a quarter into the second sub-step: by then this wave
 // holds every fragment of step j, so the barrier both frees the stages of
@@ -74,24 +76,27 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t byte_buffer(const void* p, siz
                                              0x00020000);
 }
 
-template <int WMT, int NXT, bool PAIRED = false>
+template <int WMT, int NXT, bool PAIRED = false, bool DEEP = false>
 struct TileGemm {
     static constexpr int NTH = 256;
     static constexpr int WROWS = 32 * WMT;              // weight rows of a workgroup
     static constexpr int XROWS = 32 * NXT;              // activation rows of a workgroup
     static constexpr int NP = PAIRED ? 2 : 1;
     static constexpr int XROWB = 128 * NP;              // bytes of an activation row in one stage
-    static constexpr int SW = 3;                        // weight stages (activations: two)
+    static constexpr unsigned kTailBit = 2 * kTileSpan;   // on a byte offset: past K
     static constexpr int WST = WROWS * 128;
     static constexpr int XST = XROWS * XROWB;
+    // stages of the two rings
+    static constexpr int SX = DEEP && 3 * WST + 3 * XST <= 160 * 1024 ? 3 : 2;
+    static constexpr int SW = SX == 3 && 4 * WST + 3 * XST <= 160 * 1024 ? 4 : 3;
     static constexpr int XOFF = SW * WST;
-    static constexpr int SMEM = XOFF + 2 * XST;
+    static constexpr int SMEM = XOFF + SX * XST;
     static constexpr int WI = WMT;                      // copies per wave and step
     static constexpr int XI = NXT * NP;
     static constexpr int MF = WMT * NXT * NP;           // MFMAs per sub-step
     static constexpr int NR = WMT + NXT * NP;           // fragment reads per sub-step
     static_assert(SMEM <= 160 * 1024, "LDS");
-    static_assert(2 * WI + 2 * XI < 64, "vmcnt range");
+    static_assert((SW - 1) * WI + SX * XI < 64, "vmcnt range");
     static_assert(MF - MF / 4 >= NR, "at most one read per MFMA");
 
     // accumulator (m, n) register j: weight row wrow(m) + j, activation row xrow(n)
@@ -101,7 +106,7 @@ struct TileGemm {
     int lane, wave, wa, wb;
     __amdgpu_buffer_rsrc_t rw[2], rx;   // weight copy i reads through rw[i & 1]
     unsigned wof[WI], xof[XI];          // byte offsets of this lane's pieces
-    unsigned xtail[4];                  // out-of-range bit for pieces past K in the last step (by copy % 4)
+    int krem;                           // columns of the last step, 64 where it is whole
     int step0, last;                    // first and last 64-wide step
 
     __device__ __forceinline__ int wrow(int m) const { return (wa * WMT + m) * 16 + 4 * (lane >> 4); }
@@ -135,22 +140,17 @@ struct TileGemm {
     // covers K weight columns.  Steps [s0, s1) of 64 columns.
     __device__ __forceinline__ void activations(const uint16_t* x, long ld, int rows, int K, int s0, int s1) {
         rx = byte_buffer(x, ((size_t)(rows - 1) * ld + (size_t)K * NP) * 2);
-        const int krem = K - (K - 1) / 64 * 64;   // columns of the last step
-        const bool ends = s1 * 64 >= K;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) xtail[i] = 0;
+        krem = s1 * 64 >= K ? K - (K - 1) / 64 * 64 : 64;
 #pragma unroll
         for (int i = 0; i < XI; ++i) {
             if constexpr (PAIRED) {
                 const int row = (wave * XI + i) * 4 + (lane >> 4);
                 const int ls = (lane & 15) ^ (row & 15);
                 xof[i] = row < rows ? (unsigned)((size_t)row * ld * 2) + ls * 16 : (unsigned)kTileSpan;
-                if (i < 4) xtail[i] = ends && (ls >> 1) * 8 >= krem ? (unsigned)kTileSpan : 0u;
             } else {
                 const int row = (wave * XI + i) * 8 + (lane >> 3);
                 const int ls = (lane & 7) ^ ((row >> 1) & 7);
                 xof[i] = row < rows ? (unsigned)((size_t)row * ld * 2) + ls * 16 : (unsigned)kTileSpan;
-                if (i < 4) xtail[i] = ends && ls * 8 >= krem ? (unsigned)kTileSpan : 0u;
             }
         }
         step0 = s0;
@@ -161,26 +161,50 @@ struct TileGemm {
     __device__ __forceinline__ void copy_w(int step, int slot, int i) const {
         buffer_dma16(rw[i & 1], wof[i], step * 128, lds + slot * WST + (wave * WI + i) * 1024, CPOL);
     }
-    __device__ __forceinline__ void copy_x(int step, int slot, int i, const unsigned (&tail)[4]) const {
-        buffer_dma16(rx, xof[i] | tail[i & 3], step * XROWB, lds + XOFF + slot * XST + (wave * XI + i) * 1024, 0);
+    __device__ __forceinline__ void copy_x(int step, int slot, int i) const {
+        buffer_dma16(rx, xof[i], step * XROWB, lds + XOFF + slot * XST + (wave * XI + i) * 1024, 0);
     }
-    __device__ __forceinline__ void tail_of(int step, unsigned (&tail)[4]) const {
+    // Before the copies of the last step: pieces past K go out of range, the
+    // weights' too (what lies there times a zero need not be a zero).
+    __device__ __forceinline__ void enter_w(int step) {
+        if (step != last || krem == 64) return;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tail[i] = step == last ? xtail[i] : 0u;
+        for (int i = 0; i < WI; ++i)
+            if ((((lane & 7) ^ ((wcopy_row(i) >> 1) & 7)) << 3) >= krem) wof[i] |= kTailBit;
+    }
+    __device__ __forceinline__ void enter_x(int step) {
+        if (step != last || krem == 64) return;
+#pragma unroll
+        for (int i = 0; i < XI; ++i) {
+            const int ls = PAIRED ? ((lane & 15) ^ (((wave * XI + i) * 4 + (lane >> 4)) & 15)) >> 1
+                                  : (lane & 7) ^ ((((wave * XI + i) * 8 + (lane >> 3)) >> 1) & 7);
+            if (ls * 8 >= krem) xof[i] |= kTailBit;
+        }
+    }
+    __device__ __forceinline__ void leave() {
+        if (krem == 64) return;
+#pragma unroll
+        for (int i = 0; i < WI; ++i) wof[i] &= ~kTailBit;
+#pragma unroll
+        for (int i = 0; i < XI; ++i) xof[i] &= ~kTailBit;
     }
 
-    // The copies of the first two steps (the LDS rings must be free).
+    // The copies of the first steps (the LDS rings must be free): SW - 1 of the
+    // weights, SX of the activations, in the order of the steps.
     template <int CPOL>
-    __device__ __forceinline__ void prologue() const {
+    __device__ __forceinline__ void prologue() {
+        static_assert(SW - 1 <= SX, "order of the first copies");
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < SX; ++s) {
             const int step = min(step0 + s, last);
-            unsigned tail[4];
-            tail_of(step, tail);
+            if (s < SW - 1) {
+                enter_w(step);
 #pragma unroll
-            for (int i = 0; i < WI; ++i) copy_w<CPOL>(step, s, i);
+                for (int i = 0; i < WI; ++i) copy_w<CPOL>(step, s, i);
+            }
+            enter_x(step);
 #pragma unroll
-            for (int i = 0; i < XI; ++i) copy_x(step, s, i, tail);
+            for (int i = 0; i < XI; ++i) copy_x(step, s, i);
         }
     }
 
@@ -213,7 +237,7 @@ struct TileGemm {
         for (int m = 0; m < WMT; ++m)
 #pragma unroll
             for (int n = 0; n < NXT; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        wait_vmcnt<WI + XI>();   // step step0 has landed (this wave's copies; the barrier: everyone's)
+        wait_vmcnt<(SW - 2) * WI + (SX - 1) * XI>();   // step step0 has landed (this wave's copies; the barrier: everyone's)
         block_barrier();
 #pragma unroll
         for (int t = 0; t < NR; ++t) read(0, 0, 0, 0, t);
@@ -221,10 +245,12 @@ struct TileGemm {
         constexpr int SPAN = MF - MF / 4;       // MFMAs the reads and copies are spread over
         int ws = 0, xs = 0;
         for (int j = step0; j <= last; ++j) {
-            const int ws1 = ws == 2 ? 0 : ws + 1, ws2 = ws1 == 2 ? 0 : ws1 + 1;
-            const int j2 = min(j + 2, last);   // past the end the last step is copied again, into stages nobody reads
-            unsigned tail[4];
-            tail_of(j2, tail);
+            const int ws1 = ws == SW - 1 ? 0 : ws + 1, wfree = ws == 0 ? SW - 1 : ws - 1;
+            const int xs1 = xs == SX - 1 ? 0 : xs + 1;
+            // past the end the last step is copied again, into stages nobody reads
+            const int jw = min(j + SW - 1, last), jx = min(j + SX, last);
+            enter_w(jw);
+            enter_x(jx);
             __builtin_amdgcn_sched_barrier(0);
             static_for<2 * MF>([&](auto idx) {
                 constexpr int sub = idx.value / MF, q = idx.value % MF;
@@ -234,27 +260,28 @@ struct TileGemm {
                 constexpr int xi = sub == 1 ? op_at(q, q0, SPAN, XI, 1) : -1;
                 if constexpr (sub == 1 && q == QB) {
                     // this wave holds all of step j, and its copies of step j + 1 have landed
-                    // (only the weights of step j + 2 may be out)
+                    // (weights of steps j + 2 .. j + SW - 1 and activations of j + 2 .. j + SX - 1 may be out)
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    wait_vmcnt<WI>();
+                    wait_vmcnt<(SW - 2) * WI + (SX - 2) * XI>();
                     block_barrier();
                 }
                 if constexpr (rt >= 0) {
                     if constexpr (sub == 0)
                         read(1, 1, ws, xs, rt);
                     else
-                        read(0, 0, ws1, xs ^ 1, rt);
+                        read(0, 0, ws1, xs1, rt);
                 }
-                if constexpr (wi >= 0) copy_w<CPOL>(j2, ws2, wi);
-                if constexpr (xi >= 0) copy_x(j2, xs, xi, tail);
+                if constexpr (wi >= 0) copy_w<CPOL>(jw, wfree, wi);
+                if constexpr (xi >= 0) copy_x(jx, xs, xi);
                 constexpr int m = q / (NXT * NP), qn = q % (NXT * NP);
                 constexpr int nn = (m & 1) ? NXT * NP - 1 - qn : qn;   // back and forth along the activations
                 acc[m][nn / NP] = mfma_16x16x32_bf16(af[sub][m], bf[sub][nn], acc[m][nn / NP]);
                 __builtin_amdgcn_sched_barrier(0);
             });
             ws = ws1;
-            xs ^= 1;
+            xs = xs1;
         }
+        leave();
         wait_vmcnt<0>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
