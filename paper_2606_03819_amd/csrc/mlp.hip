@@ -157,15 +157,13 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_bf16_kernel(const uint16_t* 
     }
 }
 
-// ------------------------------------------------------------------ fp32
+// ------------------------------------------------------------ plain products
 
-// one activation: fp32, or a bf16 hi/lo pair interleaved by 8
-__device__ __forceinline__ float load_act(const float* p, size_t i) { return p[i]; }
+// one activation: a bf16 hi/lo pair interleaved by 8
 __device__ __forceinline__ float load_act(const uint16_t* p, size_t i) {
     const size_t q = (i >> 3) * 16 + (i & 7);
     return bf16_bits_to_f32(p[q]) + bf16_bits_to_f32(p[q + 8]);
 }
-__device__ __forceinline__ void store_act(float* p, size_t i, float v) { p[i] = v; }
 __device__ __forceinline__ void store_act(uint16_t* p, size_t i, float v) {
     const size_t q = (i >> 3) * 16 + (i & 7);
     const uint32_t hi = f32_to_bf16_bits(v);
@@ -173,8 +171,8 @@ __device__ __forceinline__ void store_act(uint16_t* p, size_t i, float v) {
     p[q + 8] = (uint16_t)f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
 }
 
-// The approximator's fp32 products (small models), and the bf16 ones whose
-// widths pass the block-tiled kernel's offsets (tile_width_ok): out[r, n] = epi( x_r . W[n] )
+// The bf16 products whose widths pass the block-tiled kernel's offsets
+// (tile_width_ok): out[r, n] = epi( x_r . W[n] )
 // with x_r = [x0 row of r's drafter state (d0 wide) ; x1 row r (K - d0 wide)].
 // A workgroup holds 16 rows x 16 output columns; the reduction range streams
 // through LDS in 64-wide chunks (every thread copies four activation and four
@@ -256,6 +254,89 @@ __global__ __launch_bounds__(256) void mlp_simt_kernel(const T* __restrict__ wa,
         store_act(out, (size_t)r * ldo + n, a);   // an activation row: ldo elements (pairs)
     } else {
         store_elem(out, (size_t)r * ldo + n, load_elem(h, (size_t)state_of(r) * N + n) + acc_a);
+    }
+}
+
+// The approximator's fp32 products (small models), with the arguments of the
+// plain kernel above.  A handful of workgroups and one fmaf chain an output:
+// what bounds it is the chain and the round trips to memory, so a chunk is 256
+// columns wide (all of x and W for the widths such models have, in one or two
+// trips, the next chunk's in flight while one is multiplied) and LDS is read 16
+// bytes at a time.  31 rows, I = d = 256: gate/up 29.5 -> 10.3 us, down 9.6
+// -> 4.9 us against 64-wide chunks and 4-byte reads.
+template <bool GATE>
+__global__ __launch_bounds__(256) void mlp_f32_kernel(const float* __restrict__ wa, const float* __restrict__ wb, int N,
+                                                      int K, const float* __restrict__ x0, int d0,
+                                                      const float* __restrict__ x1, int ld1, RowTable rt, int rows,
+                                                      const float* __restrict__ h, float* __restrict__ out, int ldo) {
+    constexpr int KC = 256, LD = KC + 4;
+    constexpr int NW = GATE ? 2 : 1;
+    __shared__ __align__(16) float xs[16 * LD];
+    __shared__ __align__(16) float ws[NW][16 * LD];
+    const int tid = threadIdx.x;
+    const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16;
+    const int tx = tid & 15, ty = tid >> 4;
+    const bool two = GATE && wb != nullptr;
+    auto state_of = [&](int r) {
+        const int s = r / rt.Rs;
+        return s * rt.gamma + rt.depth(r - s * rt.Rs) - 1;
+    };
+    // this thread's pieces of a chunk: rows tid / 64 + 4 j, k 4 (tid % 64)
+    const int prow = tid >> 6, pk = (tid & 63) * 4;
+    int xrow[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = r0 + prow + 4 * j;
+        xrow[j] = r < rows ? state_of(r) : -1;
+    }
+    const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 px[4], pw[NW][4];
+    auto fetch = [&](int k0) {
+        const int k = k0 + pk;   // d0, K and the strides are multiples of 16
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = r0 + prow + 4 * j, n = n0 + prow + 4 * j;
+            const float* xp = k < d0 ? x0 + (size_t)xrow[j] * d0 + k : x1 + (size_t)r * ld1 + (k - d0);
+            px[j] = xrow[j] >= 0 && k < K ? *reinterpret_cast<const f32x4*>(xp) : zero;
+            const bool in = n < N && k < K;
+            pw[0][j] = in ? *reinterpret_cast<const f32x4*>(wa + (size_t)n * K + k) : zero;
+            if constexpr (GATE) pw[1][j] = in && two ? *reinterpret_cast<const f32x4*>(wb + (size_t)n * K + k) : zero;
+        }
+    };
+    float acc[NW];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) acc[q] = 0.f;
+    fetch(0);
+    for (int k0 = 0; k0 < K; k0 += KC) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            *reinterpret_cast<f32x4*>(xs + (prow + 4 * j) * LD + pk) = px[j];
+#pragma unroll
+            for (int q = 0; q < NW; ++q) *reinterpret_cast<f32x4*>(&ws[q][(prow + 4 * j) * LD + pk]) = pw[q][j];
+        }
+        __syncthreads();
+        if (k0 + KC < K) fetch(k0 + KC);
+        const int kn = min(KC, K - k0);   // a multiple of 16
+#pragma unroll 4
+        for (int k = 0; k < kn; k += 4) {
+            const f32x4 xv = *reinterpret_cast<const f32x4*>(xs + ty * LD + k);
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+                const f32x4 wv = *reinterpret_cast<const f32x4*>(&ws[q][tx * LD + k]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[q] = fmaf(xv[e], wv[e], acc[q]);
+            }
+        }
+        __syncthreads();
+    }
+    const int r = r0 + ty, n = n0 + tx;
+    if (r >= rows || n >= N) return;
+    if constexpr (GATE) {
+        float a = acc[0] / (1.0f + expf(-acc[0]));
+        if (two) a *= acc[1];
+        out[(size_t)r * ldo + n] = a;
+    } else {
+        out[(size_t)r * ldo + n] = h[(size_t)state_of(r) * N + n] + acc[0];
     }
 }
 
@@ -466,6 +547,7 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
                                  2l * I, I, I, partial, r, stream);
 }
 
+// The plain kernels: fp32, and bf16 widths past the block-tiled kernel's offsets.
 template <class T>
 static hipError_t launch_arapprox_simt(const void* h, const int32_t* root, const int32_t* context,
                                        const int32_t* topk_idx, const void* emb, const void* gain_h,
@@ -475,13 +557,21 @@ static hipError_t launch_arapprox_simt(const void* h, const int32_t* root, const
     const int rows = b * rt.Rs, ew = npre * d;
     launch_norms<T>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag, nullptr, 0,
                     stream);
-    hipLaunchKernelGGL((mlp_simt_kernel<T, true>), dim3(cdiv(I, 16), cdiv(rows, 16)), dim3(256), 0, stream,
-                       static_cast<const T*>(w_gate), static_cast<const T*>(w_up), I, (long)d + ew,
-                       static_cast<const T*>(ht), d, static_cast<const T*>(et), (long)ew, rt, rows, nullptr,
-                       static_cast<T*>(act), I);
-    hipLaunchKernelGGL((mlp_simt_kernel<T, false, true>), dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
-                       static_cast<const T*>(w_down), nullptr, d, (long)I, nullptr, 0, static_cast<const T*>(act),
-                       (long)I, rt, rows, static_cast<const T*>(h), static_cast<T*>(hp), d);
+    const dim3 gg(cdiv(I, 16), cdiv(rows, 16)), gd(cdiv(d, 16), cdiv(rows, 16));
+    const T *wg = static_cast<const T*>(w_gate), *wu = static_cast<const T*>(w_up), *wd = static_cast<const T*>(w_down);
+    const T *xh = static_cast<const T*>(ht), *xe = static_cast<const T*>(et), *hb = static_cast<const T*>(h);
+    T *ab = static_cast<T*>(act), *ob = static_cast<T*>(hp);
+    if constexpr (sizeof(T) == 4) {
+        hipLaunchKernelGGL(mlp_f32_kernel<true>, gg, dim3(256), 0, stream, wg, wu, I, d + ew, xh, d, xe, ew, rt, rows,
+                           nullptr, ab, I);
+        hipLaunchKernelGGL(mlp_f32_kernel<false>, gd, dim3(256), 0, stream, wd, nullptr, d, I, nullptr, 0, ab, I, rt,
+                           rows, hb, ob, d);
+    } else {
+        hipLaunchKernelGGL((mlp_simt_kernel<T, true>), gg, dim3(256), 0, stream, wg, wu, I, (long)d + ew, xh, d, xe,
+                           (long)ew, rt, rows, nullptr, ab, I);
+        hipLaunchKernelGGL((mlp_simt_kernel<T, false, true>), gd, dim3(256), 0, stream, wd, nullptr, d, (long)I,
+                           nullptr, 0, ab, (long)I, rt, rows, hb, ob, d);
+    }
     return hipGetLastError();
 }
 
@@ -556,19 +646,21 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
         return tile_product_finished(pe, false, wl + d, nullptr, static_cast<const uint16_t*>(et), d, 2 * d, d,
                                      mlp_partial, f, stream);
     }
-    auto simt = [&](auto zero) {
-        using T = decltype(zero);
-        launch_norms<T>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag, counters, 0,
-                        stream);
-        hipLaunchKernelGGL((mlp_simt_kernel<T, false>), dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
-                           static_cast<const T*>(w_lin), nullptr, d, 2l * d, static_cast<const T*>(ht), d,
-                           static_cast<const T*>(et), (long)d, rt, rows, static_cast<const T*>(h),
-                           static_cast<T*>(hp), d);
-    };
-    if (bf16)
-        simt(uint16_t{});
-    else
-        simt(float{});
+    const dim3 grid(cdiv(d, 16), cdiv(rows, 16));
+    if (bf16) {
+        launch_norms<uint16_t>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
+                               counters, 0, stream);
+        hipLaunchKernelGGL((mlp_simt_kernel<uint16_t, false>), grid, dim3(256), 0, stream,
+                           static_cast<const uint16_t*>(w_lin), nullptr, d, 2l * d, static_cast<const uint16_t*>(ht), d,
+                           static_cast<const uint16_t*>(et), (long)d, rt, rows, static_cast<const uint16_t*>(h),
+                           static_cast<uint16_t*>(hp), d);
+    } else {
+        launch_norms<float>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
+                            counters, 0, stream);
+        hipLaunchKernelGGL(mlp_f32_kernel<false>, grid, dim3(256), 0, stream, static_cast<const float*>(w_lin), nullptr,
+                           d, 2 * d, static_cast<const float*>(ht), d, static_cast<const float*>(et), d, rt, rows,
+                           static_cast<const float*>(h), static_cast<float*>(hp), d);
+    }
     return hipGetLastError();
 }
 

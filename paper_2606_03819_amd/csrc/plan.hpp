@@ -41,7 +41,7 @@ inline int plan_nt(int rows) { return rows <= 32 ? 1 : (rows <= 64 ? 2 : 4); }
 // workgroup per (tile range, row block), the row blocks of a range on
 // consecutive workgroups so that they share its tiles through L2.  One row
 // block: the tiles spread over TF_LM_WORKGROUPS workgroups; more row blocks:
-// the block-tiled plan above.  fp32 (small workloads, SIMT kernel): 32 rows and at most
+// the block-tiled plan above.  fp32 (small workloads, SIMT kernel): 16 rows and 1 to
 // 8 tiles (256 tokens) per workgroup.
 struct LmPlan {
     int NT, WM, NW, chunk, nrb, ntiles, nk;
@@ -192,8 +192,11 @@ inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
         p.NT = 1;
         p.WM = 2;
         p.NW = 4;
-        p.chunk = 8;
-        p.nrb = cdiv(rows, 32);
+        p.nrb = cdiv(rows, 16);
+        // slices of one tile while that is at most two workgroups a CU, of up
+        // to eight where more row blocks or a larger vocabulary fill the chip
+        p.chunk = cdiv((long long)p.nrb * p.ntiles, 2 * kNumCUs);
+        if (p.chunk > 8) p.chunk = 8;
         p.map = make_slice_map(p.ntiles, cdiv(p.ntiles, p.chunk), p.chunk);
         p.wnt = false;
     }
