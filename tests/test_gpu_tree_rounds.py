@@ -1,0 +1,110 @@
+"""Budgets that are selected in rounds (65 to 512 nodes) against a best-first
+walk on the host, which pops one node at a time and so also defines the result
+for rows that are not sorted or hold positive entries (the rounds must leave
+those to the serial selection).  Trees are compared exactly."""
+import heapq
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _walk(idx, lp, topk, gamma, k, B, marginal):
+    """One pop at a time: score desc, depth asc, rank path asc; a node's next sibling follows it into the queue."""
+    K2 = idx.shape[1]
+    out = []
+
+    def push(queue, ps, depth, row, path, rank, parent):
+        if rank < K2:
+            s = np.float32(ps) + lp[row, rank]
+            heapq.heappush(queue, (-float(s), depth, path + (rank,), float(s), row, rank, parent, ps))
+    queue = []
+    push(queue, np.float32(0), 1, 0, (), 0, -1)
+    while queue and len(out) < B:
+        _, depth, path, s, row, rank, parent, ps = heapq.heappop(queue)
+        tok = int(idx[row, rank])
+        n = len(out)
+        out.append((tok, parent, depth, s))
+        push(queue, ps, depth, row, path[:-1], rank + 1, parent)
+        if depth < gamma:
+            child = None
+            if marginal:
+                child = depth
+            else:
+                hit = np.nonzero(topk[depth - 1] == tok)[0]
+                if hit.size:
+                    child = 1 + (depth - 1) * k + int(hit[0])
+            if child is not None:
+                push(queue, np.float32(s), depth + 1, child, path, 0, n)
+    return out
+
+
+def _case(shape, gamma, k, K2, seed, marginal):
+    rng = np.random.default_rng(seed)
+    R = gamma if marginal else 1 + (gamma - 1) * k
+    depth = np.arange(R) if marginal else np.concatenate([[0], 1 + np.arange((gamma - 1) * k) // k])
+    topk = np.stack([rng.permutation(5000)[:k] for _ in range(gamma)])
+    idx = np.empty((R, K2), np.int64)
+    for r in range(R):   # the depth's candidates lead most rows
+        rest = rng.permutation(np.arange(5000, 5000 + 2 * K2))[:K2]
+        idx[r] = np.concatenate([rng.permutation(topk[depth[r]]), rest])[:K2]
+        if r % 3 == 0:
+            idx[r] = rng.permutation(idx[r])
+    lp = -1.2 * np.log1p(np.arange(K2))[None] * rng.uniform(0.6, 2.0, (R, 1)) - 0.3 + 0.3 * rng.standard_normal((R, K2))
+    lp = np.minimum(lp, -1e-3)
+    if shape == "flat":
+        lp = -9.0 - rng.random((R, K2))
+    if shape == "ties":
+        lp = np.round(lp * 2) / 2
+    if shape == "zeros":
+        lp[:, :3] = 0.0
+    lp = -np.sort(-lp, axis=1).astype(np.float32)
+    if shape == "tail":   # a list whose rest is impossible
+        lp[:, K2 // 5:] = -np.inf
+    if shape == "unsorted":
+        lp[1 + seed % (R - 1), 2] = 0.0
+        lp[0, K2 // 2] = -0.5
+    if shape == "positive":
+        lp[2 % R, 0] = 1.5
+    return idx.astype(np.int32), lp.astype(np.float32), topk.astype(np.int32)
+
+
+@pytest.mark.parametrize("shape,gamma,k,K2,B", [
+    ("peaked", 16, 8, 256, 256), ("peaked", 16, 8, 65, 65), ("peaked", 9, 3, 40, 512), ("peaked", 16, 40, 128, 128),
+    ("peaked", 1, 4, 300, 300), ("peaked", 3, 2, 30, 150), ("peaked", 12, 16, 300, 300), ("peaked", 16, 8, 512, 400),
+    ("flat", 16, 8, 256, 256), ("ties", 8, 4, 100, 100), ("ties", 16, 8, 256, 512), ("zeros", 6, 4, 80, 80),
+    ("tail", 6, 4, 100, 300), ("unsorted", 8, 4, 100, 100), ("positive", 8, 4, 100, 100), ("unsorted", 16, 20, 70, 70),
+])
+@pytest.mark.parametrize("marginal", [False, True])
+def test_rounds_pop_what_the_walk_pops(shape, gamma, k, K2, B, marginal):
+    import torch
+    from paper_2606_03819_amd import binding
+    if marginal and shape in ("unsorted", "positive") and gamma < 3:
+        pytest.skip("needs a second row")
+    cases = [_case(shape, gamma, k, K2, seed, marginal) for seed in (1, 2)]
+    idx, lp, topk = (torch.from_numpy(np.stack(x)).cuda() for x in zip(*cases))
+    if marginal:
+        got = binding.treeflash_build_tree_marginal(idx, lp, B)
+    else:
+        got = binding.treeflash_build_tree(idx, lp, topk, B)
+    for s, (i, p, t) in enumerate(cases):
+        want = _walk(i, p, t, gamma, k, B, marginal)
+        n = len(want)
+        for f, name in enumerate(("token", "parent", "depth", "score")):
+            g = got[name][s].cpu().numpy()
+            assert g[:n].tolist() == [w[f] for w in want], f"{name} differs"
+        assert (got["token"][s, n:] == -1).all() and (got["depth"][s, n:] == 0).all()
+
+
+def test_rounds_leave_nan_to_the_serial_selection():
+    """A best-first tree's first 64 nodes are the tree of budget 64, which is always selected serially."""
+    import torch
+    from paper_2606_03819_amd import binding
+    for at in ((0, 3), (2, 0), (5, 20)):
+        i, p, t = _case("peaked", 8, 4, 100, 3, False)
+        p[at] = np.nan
+        idx, lp, topk = (torch.from_numpy(x[None]).cuda() for x in (i, p, t))
+        small, large = (binding.treeflash_build_tree(idx, lp, topk, B) for B in (64, 100))
+        for f in ("token", "parent", "depth"):
+            assert torch.equal(small[f], large[f][:, :64]), f
