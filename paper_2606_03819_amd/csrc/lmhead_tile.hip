@@ -1,4 +1,4 @@
-// LM head for more than 128 activation rows (bf16): the block-tiled GEMM with
+// LM head on the block-tiled GEMM (bf16; which calls: see lm_plan), with
 // the list epilogue, one (row, vocabulary slice) partial per round.
 #include "common.hpp"
 #include "launch.hpp"
@@ -25,7 +25,7 @@ struct LmTileArgs {
 // copies leave alone.
 template <int WMT, int NXT, bool WNT, bool LONG>
 __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(LmTileArgs a) {
-    using G = TileGemm<WMT, NXT>;
+    using G = TileGemm<WMT, NXT, false, (NXT <= 4)>;
     using E = EpiLmTile<WMT, NXT, LONG>;
     static_assert(E::SMEM <= G::WST, "the epilogue's lists fit one weight stage");
     constexpr int CPOL = WNT ? kCpolNt : 0;
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(LmTileArgs a) {
         const int slice = range * a.map.rmax + r;
         more = ++r < a.map.rmax && weights(r);
         if (more) g.template prologue<CPOL>();
-        E::apply(g, dyn + 2 * G::WST, vbase, vend, row0, a.R, slice, a.nslices, a.sl2, a.part);
+        E::apply(g, dyn + (G::SW - 1) * G::WST, vbase, vend, row0, a.R, slice, a.nslices, a.sl2, a.part);
     }
     // empty slices: partials the merge skips
     for (; r < a.map.rmax; ++r) {
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, 1) void lmhead_tile_kernel(LmTileArgs a) {
 
 template <int WMT, int NXT, bool WNT>
 static hipError_t launch_shape(const LmTileArgs& a, int blocks, bool longl, hipStream_t st) {
-    using G = TileGemm<WMT, NXT>;
+    using G = TileGemm<WMT, NXT, false, (NXT <= 4)>;
     auto kern = longl ? lmhead_tile_kernel<WMT, NXT, WNT, true> : lmhead_tile_kernel<WMT, NXT, WNT, false>;
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, G::SMEM);
@@ -94,6 +94,14 @@ hipError_t launch_lm_tile(const LmPlan& p, const uint16_t* x, long ldx, const ui
     TF_LM_TILE_CASE(8, 6, true);
     TF_LM_TILE_CASE(7, 6, true);
     TF_LM_TILE_CASE(6, 6, true);
+    TF_LM_TILE_CASE(8, 4, true);
+    TF_LM_TILE_CASE(7, 4, true);
+    TF_LM_TILE_CASE(6, 4, true);
+    TF_LM_TILE_CASE(4, 4, true);
+    TF_LM_TILE_CASE(8, 2, true);
+    TF_LM_TILE_CASE(7, 2, true);
+    TF_LM_TILE_CASE(6, 2, true);
+    TF_LM_TILE_CASE(4, 2, true);
 #undef TF_LM_TILE_CASE
     return hipErrorInvalidValue;
 }

@@ -112,14 +112,22 @@ inline int lm_nw(int NT) { return NT == 1 ? TF_LM_NW_NT1 : (NT == 2 ? TF_LM_NW_N
 inline int lm_wm(int NT) { return NT == 1 ? TF_LM_WM_NT1 : (NT == 2 ? TF_LM_WM_NT2 : TF_LM_WM_NT4); }
 
 // The block-tiled kernel serves bf16 calls of more rows than one 128-row block
-// (widths up to kTileMaxK keep its byte offsets in 30 bits).
+// (widths up to kTileMaxK keep its byte offsets in 30 bits), and of fewer where
+// the vocabulary gives a CU at most 7 or 8 tiles (one round of just those tiles;
+// the streaming kernels' rounds of 10 or 12 copy and multiply repeats of the
+// last tile) or where the width is no multiple of 64.  us, streaming / tiled:
+// 16 rows x 32000 x 4096 74 / 56, x 50000 x 2048 50 / 47, 8 x 64000 x 1024
+// (8 tiles a CU) 29.3 / 30.1; 48 x 32000 x 4096 77 / 61; 64 x 65000 x 2048
+// 86 / 84; 121 x 60000 x 4096 119 / 112; several rounds: 121 x 151936 x 4096
+// 233 / 247; width 2000: 121 x 100000 149 / 131, 48 x 151936 199 / 204.
 constexpr int kTileMinRows = 129;
 constexpr int kTileMaxK = 1 << 20;
 
 // Row blocks of at most 256 rows, 192 where the rows then fill them (a wave
-// grid of 2 x 2 waves of 16-row tiles: NXT = 8 or 6).  One row block streams
+// grid of 2 x 2 waves of 16-row tiles: NXT = 8 or 6; 4 and 2 for up to 128 and
+// 64 rows).  One row block streams
 // the vocabulary once and is as much HBM- as MFMA-bound: the tiles are spread
-// evenly over the CUs, in rounds of 6, 7 or 8 tiles, whichever leaves the
+// evenly over the CUs, in rounds of 6, 7 or 8 tiles (4 too for few rows), whichever leaves the
 // least work for padding (a round's epilogue counted as one more tile), while
 // that makes no more slices than long lists may have.  Otherwise, and for
 // more row blocks: one slice of 8 tiles per workgroup.
@@ -130,7 +138,7 @@ inline LmPlan lm_tile_plan(int rows, int V, int d) {
     p.dma = false;
     p.tile = true;
     p.nrb = cdiv(rows, 256);
-    p.NT = cdiv(rows, p.nrb * 32) <= 6 ? 6 : 8;
+    p.NT = rows <= 64 ? 2 : rows <= 128 ? 4 : (cdiv(rows, p.nrb * 32) <= 6 ? 6 : 8);
     p.nrb = cdiv(rows, 32 * p.NT);
     p.NW = 4;
     p.WB = 2;
@@ -139,8 +147,8 @@ inline LmPlan lm_tile_plan(int rows, int V, int d) {
     if (p.nrb == 1) {
         const int G = p.ntiles < kNumCUs ? p.ntiles : kNumCUs;
         const int per = cdiv(p.ntiles, G);
-        for (int wm = 7; wm >= 6; --wm)
-            if (cdiv(per, wm) * (wm + 1) < cdiv(per, p.WM) * (p.WM + 1)) p.WM = wm;
+        for (int wm = 7; wm >= (p.NT <= 4 ? 4 : 6); --wm)
+            if (wm != 5 && cdiv(per, wm) * (wm + 1) < cdiv(per, p.WM) * (p.WM + 1)) p.WM = wm;
         p.map = make_slice_map(p.ntiles, G, p.WM);
     }
     if (p.nrb > 1 || p.nsplit() > kMaxSplitsLong) {
@@ -155,7 +163,9 @@ inline LmPlan lm_tile_plan(int rows, int V, int d) {
 // for callers whose scratch is short; also taken for vocabularies whose
 // block-tiled slices would be too many for long lists.
 inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
-    if (bf16 && rows >= kTileMinRows && d <= kTileMaxK) {
+    const int per = cdiv(cdiv(V, 32), kNumCUs);   // weight tiles per CU
+    const bool few = per > 1 && (per <= (rows <= 32 ? 7 : 8) || (rows > 64 && d % TF_LM_DMA_KC != 0));
+    if (bf16 && d <= kTileMaxK && (rows >= kTileMinRows || (few && !lean))) {
         const LmPlan t = lm_tile_plan(rows, V, d);
         if (rows > 256 || (!lean && t.nsplit() <= kMaxSplitsLong)) return t;
     }

@@ -1,4 +1,4 @@
-"""The LM head's block-tiled kernel (more than 128 rows) on small shapes.
+"""The LM head's block-tiled kernel on small shapes.
 
 Operands are small integers (and a power of two), so every logit is exact in
 any order of the sums and carries many ties: the lists must equal a stable
@@ -42,6 +42,22 @@ def test_lm_head_tile_is_the_stable_sort(rows, V, d, k):
     import torch
     from paper_2606_03819_amd import binding
     h, lm = _case(rows, V, d, rows + V, 2 if d < 512 else 1)
+    lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
+    idx, lp = binding.treeflash_marginal_topk(h, lm, k, lse=lse)
+    _check(h, lm, k, idx, lp, lse)
+
+
+# at most 128 rows: vocabularies of 2 to 8 tiles a CU (slices of 4, 6, 7 and 8
+# tiles, ragged last tiles and CUs without one), and widths that are no multiple
+# of 64 over several rounds
+@pytest.mark.parametrize("rows,V,d,k", [
+    (1, 8193, 64, 8), (16, 33000, 80, 16), (32, 57344, 128, 100), (33, 40961, 64, 32), (64, 65536, 192, 64),
+    (65, 16384, 48, 32), (97, 50021, 320, 70), (128, 57345, 64, 16), (121, 70001, 112, 32),
+])
+def test_lm_head_tile_few_rows(rows, V, d, k):
+    import torch
+    from paper_2606_03819_amd import binding
+    h, lm = _case(rows, V, d, rows + V, 2)
     lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
     idx, lp = binding.treeflash_marginal_topk(h, lm, k, lse=lse)
     _check(h, lm, k, idx, lp, lse)
