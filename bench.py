@@ -273,8 +273,8 @@ def mlp_kernel_bytes(w):
     gate = nproj * I * (d + ew) * es + (S * d + R * ew) * es + R * 2 * I * es
     down = d * I * es + R * 2 * I * es + S * d * es + R * d * es
     norm = S * d * es + R * ew * es + 2 * d * es + (S * d + R * ew) * es
-    return [(r"mlp_dma_kernel<\d+, \d+, false,", "gate/up (or gate) projection: `mlp_dma_kernel<..., false, ...>`", gate),
-            (r"mlp_dma_kernel<\d+, \d+, true,", "down projection: `mlp_dma_kernel<..., true, ...>`", down),
+    return [(r"mlp_dma_kernel<", "gate/up (or gate) projection: `mlp_dma_kernel`", gate),
+            (r"tile_product_kernel<\d+, \d+, true", "down projection: `tile_product_kernel<..., true>`", down),
             (r"rmsnorm_rows", "gather + RMSNorm: `rmsnorm_rows_bf16_kernel`", norm)]
 
 

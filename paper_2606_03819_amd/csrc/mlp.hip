@@ -373,15 +373,10 @@ static void launch_norms(const void* h, const int32_t* root, const int32_t* cont
 // ------------------------------------------------ one row block (mlp_dma.hpp)
 
 // Ring depths: SW - 1 weight stages in flight (TG tiles of 4 KiB each) and
-// two activation chunks.  Every copy of a workgroup fills LDS through the
-// same per-CU path (~45 GB/s measured for weights and activations alike), so
-// the down projection, whose 256-byte activation rows make the activation
-// four fifths of its bytes, keeps three weight stages in flight (measured
-// faster than four or five); the input projections are insensitive to
-// four to six.
-template <int TG, bool PAIRED, int NTE>
+// two activation chunks (four to six weight stages measured equal).
+template <int NTE>
 constexpr int mlp_dma_sw() {
-    return PAIRED ? 4 : (TG == 2 ? 10 : (NTE == 8 ? 4 : 5));
+    return NTE == 8 ? 4 : 5;
 }
 // activation stages: eight tiles' 32 KiB chunks leave room for one in flight
 template <int NTE>
@@ -389,12 +384,12 @@ constexpr int mlp_dma_sx() {
     return NTE == 8 ? 2 : 3;
 }
 
-template <int TG, int NTE, bool PAIRED, int WMAP, int EPI>
+template <int TG, int NTE, int WMAP, int EPI>
 static hipError_t launch_mlp_dma_nte(const MlpDmaArgs& a, hipStream_t st) {
-    constexpr int SW = mlp_dma_sw<TG, PAIRED, NTE>(), SX = mlp_dma_sx<NTE>();
-    using T = MlpDmaTraits<TG, NTE, PAIRED, SW, SX>;
+    constexpr int SW = mlp_dma_sw<NTE>(), SX = mlp_dma_sx<NTE>();
+    using T = MlpDmaTraits<TG, NTE, SW, SX>;
     static_assert(T::SMEM <= 152 * 1024, "LDS of one workgroup");
-    auto kern = mlp_dma_kernel<TG, NTE, PAIRED, SW, SX, WMAP, EPI>;
+    auto kern = mlp_dma_kernel<TG, NTE, SW, SX, WMAP, EPI>;
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, T::SMEM);
     if (e != hipSuccess) return e;
@@ -402,17 +397,17 @@ static hipError_t launch_mlp_dma_nte(const MlpDmaArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <bool PAIRED, int WMAP, int EPI>
+template <int WMAP, int EPI>
 static hipError_t launch_mlp_dma(const MlpDmaArgs& a, const MlpDmaPlan& p, hipStream_t st) {
-    constexpr int TG = PAIRED ? TF_MLP_DMA_TG_DOWN : TF_MLP_DMA_TG_IN;
+    constexpr int TG = TF_MLP_DMA_TG_IN;
     if (p.TG != TG) return hipErrorInvalidValue;
-    if (p.NTE == 1) return launch_mlp_dma_nte<TG, 1, PAIRED, WMAP, EPI>(a, st);
-    if (p.NTE == 2) return launch_mlp_dma_nte<TG, 2, PAIRED, WMAP, EPI>(a, st);
-    if constexpr (!PAIRED && EPI != kMlpEpiResidual) {   // eight tiles: the input projections only
-        if (p.NTE == 8) return launch_mlp_dma_nte<TG, 8, PAIRED, WMAP, EPI>(a, st);
+    if (p.NTE == 1) return launch_mlp_dma_nte<TG, 1, WMAP, EPI>(a, st);
+    if (p.NTE == 2) return launch_mlp_dma_nte<TG, 2, WMAP, EPI>(a, st);
+    if constexpr (EPI != kMlpEpiResidual) {   // eight tiles: the input projections only
+        if (p.NTE == 8) return launch_mlp_dma_nte<TG, 8, WMAP, EPI>(a, st);
     }
     if (p.NTE != 4) return hipErrorInvalidValue;
-    return launch_mlp_dma_nte<TG, 4, PAIRED, WMAP, EPI>(a, st);
+    return launch_mlp_dma_nte<TG, 4, WMAP, EPI>(a, st);
 }
 
 static MlpDmaArgs mlp_dma_args(const MlpDmaPlan& p, const uint16_t* w, const uint16_t* wu, int N, int Kw,
@@ -421,16 +416,6 @@ static MlpDmaArgs mlp_dma_args(const MlpDmaPlan& p, const uint16_t* w, const uin
     return MlpDmaArgs{w,     wu,    N,   Kw,   xh,   xe,   lde, Rh,   Re,      p.ntiles, p.items, p.nkh,
                       p.nke, p.G,   p.wh, p.we, out, Nout, h,  rt,   partial, counter};
 }
-
-// Eq. 1 (or the plain SiLU MLP when w_up is null) for at most 128 rows and
-// 32 drafter states: gate/up with the h~ half once per drafter state, then
-// the down projection with the residual.
-static hipError_t launch_arapprox_dma(const void* h, const int32_t* root, const int32_t* context,
-                                      const int32_t* topk_idx, const void* emb, const void* gain_h,
-                                      const void* gain_e, const void* w_gate, const void* w_up, const void* w_down,
-                                      int b, int d, int I, int V, const RowTable& rt, int npre, float eps, void* ht,
-                                      void* et, void* act, void* hp, float* partial, int* counters, int* diag,
-                                      hipStream_t stream);
 
 // One product with its finished outputs: from the accumulators, or from the
 // splits' tables.
@@ -453,9 +438,10 @@ static hipError_t tile_product_finished(const TilePlan& p, bool paired, const ui
     return launch_tile_finish(f, st);
 }
 
-// Eq. 1 on the block-tiled products: more rows than one row block, or widths
-// or states that the one-row-block kernels do not take.  The input projection
-// is split at the h~ / e~ boundary (the h~ half once per drafter state); the
+// Eq. 1 in bf16.  The down projection runs on the block-tiled kernel; so do the
+// input projections that the one-row-block kernel does not take (more rows,
+// more states, other widths), split at the h~ / e~ boundary of x (the h~ half
+// once per drafter state); the
 // bigram rows, which combine few distinct tokens in many pairs, have it split
 // once more, at the previous token's boundary, and computed once per token
 // (at 16 x 8 candidates 122 tokens for 905 rows, a seventh of the products).
@@ -468,6 +454,7 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
     const bool swiglu = w_up != nullptr;
     const int rows = b * rt.Rs, states = b * rt.gamma;
     const int N = swiglu ? 2 * I : I;
+    const int npre = rt.bigram ? 2 : 1, ew = npre * d;
     const uint16_t* hb = static_cast<const uint16_t*>(h);
     const uint16_t* htb = static_cast<const uint16_t*>(ht);
     const uint16_t* etb = static_cast<const uint16_t*>(et);
@@ -484,7 +471,15 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
     f.states = states;
     f.rt = rt;
     hipError_t e;
-    if (rt.bigram) {
+    if (mlp_dma_gate_applies(true, b, rt.gamma, rt.Rs, d, I, ew, rt.bigram)) {
+        const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, ew, I, swiglu);
+        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
+                               counters, pg.items, stream);
+        const MlpDmaArgs ag = mlp_dma_args(pg, wg, wu, I, d + ew, htb, etb, ew, states, rows, actb, I, hb, rt, partial,
+                                           counters);
+        e = swiglu ? launch_mlp_dma<kMlpWGateUp, kMlpEpiSwiGLU>(ag, pg, stream)
+                   : launch_mlp_dma<kMlpWPlain, kMlpEpiSiLU>(ag, pg, stream);
+    } else if (rt.bigram) {
         const RowTable tt = make_token_table(rt.gamma, rt.M);
         const int tokens = b * tt.Rs;
         launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, tt, 1, eps, ht, et, diag,
@@ -507,15 +502,6 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
         f.t1 = t1;
         f.t2 = t2;
         e = launch_tile_finish(f, stream);
-    } else if (mlp_dma_gate_applies(true, b, rt.gamma, rt.Rs, d, I, d)) {
-        // 129-256 rows of one or two sequences: the one-row-block kernel with eight activation tiles
-        const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, d, I, swiglu);
-        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
-                               counters, pg.items, stream);
-        const MlpDmaArgs ag = mlp_dma_args(pg, wg, wu, I, 2 * d, htb, etb, d, states, rows, actb, I, hb, rt, partial,
-                                           counters);
-        e = swiglu ? launch_mlp_dma<false, kMlpWGateUp, kMlpEpiSwiGLU>(ag, pg, stream)
-                   : launch_mlp_dma<false, kMlpWPlain, kMlpEpiSiLU>(ag, pg, stream);
     } else {
         launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
                                counters, 0, stream);
@@ -585,9 +571,6 @@ hipError_t launch_arapprox(const void* h, const int32_t* root, const int32_t* co
     const int ew = npre * d;
     const int rows = b * rt.Rs;
     if (bf16) {
-        if (mlp_dma_applies(true, b, gamma, rt.Rs, d, I, ew))
-            return launch_arapprox_dma(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d,
-                                       I, V, rt, npre, eps, ht, et, act, hp, mlp_partial, counters, diag, stream);
         if (tile_width_ok(d, ew, I))
             return launch_arapprox_tile(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d,
                                         I, V, rt, eps, ht, et, act, hp, mlp_partial, counters, hh, diag, stream);
@@ -604,7 +587,7 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
                                   float* mlp_partial, int* counters, float* hh, int* diag, hipStream_t stream) {
     const RowTable rt = make_row_table(gamma, k, 0);
     const int rows = b * rt.Rs;
-    if (mlp_dma_applies(bf16, b, gamma, rt.Rs, d, 64, d)) {
+    if (mlp_dma_linear_applies(bf16, b, gamma, rt.Rs, d)) {
         // one row block: the h~ half once per drafter state, residual epilogue
         const MlpDmaPlan pl = mlp_dma_linear_plan(rows, d);
         launch_norms<uint16_t>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
@@ -614,7 +597,7 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
                                            static_cast<const uint16_t*>(ht), static_cast<const uint16_t*>(et), d,
                                            b * gamma, rows, static_cast<uint16_t*>(hp), d, hb, rt, mlp_partial,
                                            counters);
-        return launch_mlp_dma<false, kMlpWPlain, kMlpEpiResidual>(al, pl, stream);
+        return launch_mlp_dma<kMlpWPlain, kMlpEpiResidual>(al, pl, stream);
     }
     const bool tile = bf16 && tile_width_ok(d, d, d);
     if (tile) {
@@ -662,33 +645,6 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
                            static_cast<const float*>(h), static_cast<float*>(hp), d);
     }
     return hipGetLastError();
-}
-
-static hipError_t launch_arapprox_dma(const void* h, const int32_t* root, const int32_t* context,
-                                      const int32_t* topk_idx, const void* emb, const void* gain_h,
-                                      const void* gain_e, const void* w_gate, const void* w_up, const void* w_down,
-                                      int b, int d, int I, int V, const RowTable& rt, int npre, float eps, void* ht,
-                                      void* et, void* act, void* hp, float* partial, int* counters, int* diag,
-                                      hipStream_t stream) {
-    const int ew = npre * d;
-    const int rows = b * rt.Rs;
-    const bool swiglu = w_up != nullptr;
-    const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, ew, I, swiglu);
-    const MlpDmaPlan pd = mlp_dma_down_plan(rows, d, I);
-    launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
-                           counters, pg.items + pd.items, stream);
-    const uint16_t* hb = static_cast<const uint16_t*>(h);
-    const uint16_t* htb = static_cast<const uint16_t*>(ht);
-    const uint16_t* etb = static_cast<const uint16_t*>(et);
-    uint16_t* actb = static_cast<uint16_t*>(act);
-    const MlpDmaArgs ag = mlp_dma_args(pg, static_cast<const uint16_t*>(w_gate), static_cast<const uint16_t*>(w_up),
-                                       I, d + ew, htb, etb, ew, b * rt.gamma, rows, actb, I, hb, rt, partial, counters);
-    hipError_t e = swiglu ? launch_mlp_dma<false, kMlpWGateUp, kMlpEpiSwiGLU>(ag, pg, stream)
-                          : launch_mlp_dma<false, kMlpWPlain, kMlpEpiSiLU>(ag, pg, stream);
-    if (e != hipSuccess) return e;
-    const MlpDmaArgs ad = mlp_dma_args(pd, static_cast<const uint16_t*>(w_down), nullptr, d, I, nullptr, actb, 2l * I,
-                                       0, rows, static_cast<uint16_t*>(hp), d, hb, rt, partial, counters + pg.items);
-    return launch_mlp_dma<true, kMlpWPlain, kMlpEpiResidual>(ad, pd, stream);
 }
 
 }  // namespace tf

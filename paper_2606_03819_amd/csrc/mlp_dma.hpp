@@ -1,6 +1,5 @@
-// The AR approximator's products when one activation row block holds every
-// conditional row (at most 128 rows, at most 32 drafter states): the batch-1
-// drafting step.
+// The AR approximator's input projections (and its linear layer) for at most
+// 256 conditional rows and 32 drafter states: the batch-1 drafting step.
 //
 // Every product streams a weight matrix once against few activation rows, so
 // it is bound by HBM.  An item is TG weight tiles of 32 rows over the whole
@@ -8,8 +7,9 @@
 // units of all items are dealt out in contiguous ranges to G workgroups, so
 // every workgroup streams the same weight bytes.  An item cut by a range
 // boundary is computed in pieces whose sums the last piece to arrive adds
-// in piece order (the same device-coherent hand-off as the SwiGLU products
-// of several row blocks).
+// in piece order.  The pieces may sit on different XCDs, whose L2 caches are
+// not coherent with each other; a device-scope fence would write back and
+// invalidate a whole L2, so only the sums are stored and loaded device-coherent.
 //
 // The reduction range has up to two phases (Eq. 1, x = [h~ ; e~]):
 //   h phase  columns 0..d-1 of W_gate / W_up / W_lin against the b*gamma
@@ -17,8 +17,7 @@
 //            sequence shares h~_i, so this half is computed once per
 //            (sequence, depth) on one 32-row activation tile;
 //   e phase  the remaining columns against the rows' own inputs: the
-//            normalised previous-token embeddings e~ (gate/up, SiLU, linear)
-//            or the SwiGLU activation as bf16 hi/lo pairs (down projection).
+//            normalised previous-token embeddings e~.
 // The epilogue adds the h-phase sum of a row's (sequence, depth) state to its
 // e-phase sum, so the result is the full product over x.
 //
@@ -73,19 +72,19 @@ struct MlpDmaArgs {
 // 16-byte slot swizzle of 128-byte rows (below)
 __device__ __forceinline__ int mlp_swz128(int r) { return (r >> 1) & 7; }
 
-template <int TG, int NTE, bool PAIRED, int SW, int SX>
+template <int TG, int NTE, int SW, int SX>
 struct MlpDmaTraits {
     static constexpr int NTHREADS = 256;
     static constexpr int WTILE = 32 * 128;                  // one weight tile of one stage (64 columns)
     static constexpr int WSTAGE = TG * WTILE;
-    static constexpr int XROWB = PAIRED ? 256 : 128;        // bytes of an activation row in one stage
+    static constexpr int XROWB = 128;                       // bytes of an activation row in one stage
     static constexpr int XRPI = 1024 / XROWB;               // activation rows per DMA instruction
     static constexpr int XSTAGE_E = 32 * NTE * XROWB;
     static constexpr int XSTAGE_H = 32 * 128;
     static constexpr int XSTAGE = XSTAGE_E > XSTAGE_H ? XSTAGE_E : XSTAGE_H;
     static constexpr int XOFF = SW * WSTAGE;
     static constexpr int RING = SW * WSTAGE + SX * XSTAGE;
-    static constexpr int QS = PAIRED ? 8 : 4;               // MFMA k sub-steps per chunk (e phase)
+    static constexpr int QS = 4;                            // MFMA k sub-steps per chunk (e phase)
     // every wave copies a quarter of each chunk (8-row blocks of 1 KiB)
     static constexpr int WPW = TG;                          // weight DMA instructions per wave per chunk
     static constexpr int XPW_H = 1;                         // activation DMA instructions per wave (h phase)
@@ -107,11 +106,9 @@ struct MlpDmaTraits {
     static_assert(NTE == 1 || NTE == 2 || NTE == 4 || NTE == 8, "activation tiles");
     static_assert(XPW_E >= 1 && XSTAGE_E % 4096 == 0, "whole DMA instructions per wave");
     static_assert(SW > SX && SX >= 2, "ring depths: a chunk's weights are copied before its activations");
-    // 16-byte slot swizzles: 128-byte rows (weights, plain activations) and
-    // 256-byte rows (paired activations) keep a quarter-wave's 16 fragment
-    // reads at one logical slot on 16 distinct bank groups
+    // 16-byte slot swizzle of the 128-byte rows: keeps a quarter-wave's 16
+    // fragment reads at one logical slot on 16 distinct bank groups
     __device__ static __forceinline__ int swz128(int r) { return mlp_swz128(r); }
-    __device__ static __forceinline__ int swz256(int r) { return r & 15; }
 };
 
 // ------------------------------------------------------------------ outputs
@@ -127,13 +124,13 @@ struct MlpDmaTraits {
 struct MlpLdsSums {
     const float* hs;
     const float* es;
-    template <int TG, int NTE, bool HASH>
+    template <int TG, int NTE>
     __device__ __forceinline__ void get(int t, int n, int c, int hr, int jbase, float (&v)[8]) const {
 #pragma unroll
         for (int e2 = 0; e2 < 8; ++e2) {
             const int j = jbase + (e2 & 3), hi = 32 * (e2 >> 2);
             float x = es[(t * NTE + n) * 1024 + j * 64 + c + hi];
-            if constexpr (HASH) x += hs[t * 1024 + j * 64 + hr + hi];
+            x += hs[t * 1024 + j * 64 + hr + hi];
             v[e2] = x;
         }
     }
@@ -144,7 +141,7 @@ struct MlpLdsSums {
 // 256 is a multiple of 32 NTE, so a thread keeps one row (and its drafter
 // state) for every unit.  The residual rows are read before any sum, the
 // sums of a unit are all loaded before the arithmetic.
-template <int TG, int NTE, int EPI, bool HASH, class Src>
+template <int TG, int NTE, int EPI, class Src>
 __device__ __forceinline__ void mlp_epilogue(const MlpDmaArgs& a, int item, const Src& src) {
     constexpr int GPT = EPI == kMlpEpiSwiGLU ? 2 : 4;   // groups of 8 outputs per tile
     constexpr int NE = 32 * NTE * TG * GPT;             // units of the item
@@ -183,7 +180,7 @@ __device__ __forceinline__ void mlp_epilogue(const MlpDmaArgs& a, int item, cons
             const Unit u = unit(it);
             if (!u.ok) continue;
             float v[8];
-            src.template get<TG, NTE, HASH>(u.t, u.r >> 5, u.r & 31, u.hr, 4 * u.q, v);
+            src.template get<TG, NTE>(u.t, u.r >> 5, u.r & 31, u.hr, 4 * u.q, v);
             u32x4 o;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -201,9 +198,9 @@ __device__ __forceinline__ void mlp_epilogue(const MlpDmaArgs& a, int item, cons
             // activation i0..i0+7 as bf16 hi/lo pairs interleaved by 8
             const int i0 = EPI == kMlpEpiSwiGLU ? u.tile * 16 + 8 * u.q : u.tile * 32 + 8 * u.q;
             float gv[8], uv[8];
-            src.template get<TG, NTE, HASH>(u.t, u.r >> 5, u.r & 31, u.hr, 4 * u.q, gv);
+            src.template get<TG, NTE>(u.t, u.r >> 5, u.r & 31, u.hr, 4 * u.q, gv);
             if constexpr (EPI == kMlpEpiSwiGLU)   // up rows 16.. of the tile
-                src.template get<TG, NTE, HASH>(u.t, u.r >> 5, u.r & 31, u.hr, 4 * u.q + 8, uv);
+                src.template get<TG, NTE>(u.t, u.r >> 5, u.r & 31, u.hr, 4 * u.q + 8, uv);
             u32x4 hi4, lo4;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -244,7 +241,7 @@ __device__ __forceinline__ void mlp_copy_w(const uint16_t* const (&wsrc)[TG], in
 
 // One chunk of activations: this wave's 8-row block of the h~ rows in the h
 // phase, else its DMA instructions q = c + 4v of the e-phase rows.
-template <int XPW_E, bool PAIRED>
+template <int XPW_E>
 __device__ __forceinline__ void mlp_copy_x(const uint16_t* hsrc, const uint16_t* const (&esrc)[XPW_E], bool hphase,
                                            int chunk, unsigned char* st, int c) {
     if (hphase) {
@@ -252,7 +249,7 @@ __device__ __forceinline__ void mlp_copy_x(const uint16_t* hsrc, const uint16_t*
     } else {
 #pragma unroll
         for (int v = 0; v < XPW_E; ++v)
-            dma16(esrc[v] + (long)(PAIRED ? 128 : 64) * chunk, st + (c + 4 * v) * 1024, 0);
+            dma16(esrc[v] + 64l * chunk, st + (c + 4 * v) * 1024, 0);
     }
 }
 
@@ -278,12 +275,12 @@ __device__ __forceinline__ int mlp_wait_count(int s, int nsteps, int c0, int nkh
 
 // The copies of (emulated) step s: activations of chunk s + SX - 1 (when that
 // is a chunk of the segment), then weights of chunk s + SW - 1.
-template <class T, int SW, int SX, bool PAIRED, int TG = T::TW * 2>
+template <class T, int SW, int SX, int TG = T::TW * 2>
 __device__ __forceinline__ void mlp_step_copies(MlpCursor& cur, int s, int nsteps, int c0, int nkh, int c,
                                                 const uint16_t* const (&wsrc)[TG], const uint16_t* hsrc,
                                                 const uint16_t* const (&esrc)[T::XPW_E], unsigned char* dyn) {
     if (s + SX - 1 >= 0 && cur.xnext < nsteps) {
-        mlp_copy_x<T::XPW_E, PAIRED>(hsrc, esrc, c0 + cur.xnext < nkh, cur.xnext,
+        mlp_copy_x<T::XPW_E>(hsrc, esrc, c0 + cur.xnext < nkh, cur.xnext,
                                      dyn + T::XOFF + cur.xstage * T::XSTAGE, c);
         ++cur.xnext;
         cur.xstage = cur.xstage + 1 == SX ? 0 : cur.xstage + 1;
@@ -298,13 +295,13 @@ __device__ __forceinline__ void mlp_step_copies(MlpCursor& cur, int s, int nstep
 // The start of step s: wait for this wave's copies of chunk s, meet the
 // barrier (every wave's copies have landed; the stages chunk s - 1 used are
 // free), then copy into the freed stages.
-template <class T, int SW, int SX, bool PAIRED, int TG = T::TW * 2>
+template <class T, int SW, int SX, int TG = T::TW * 2>
 __device__ __forceinline__ void mlp_step_begin(MlpCursor& cur, int s, int nsteps, int c0, int nkh, int c,
                                                const uint16_t* const (&wsrc)[TG], const uint16_t* hsrc,
                                                const uint16_t* const (&esrc)[T::XPW_E], unsigned char* dyn) {
     wait_vmcnt_dyn(mlp_wait_count<T, SW, SX>(s, nsteps, c0, nkh));
     block_barrier();
-    mlp_step_copies<T, SW, SX, PAIRED>(cur, s, nsteps, c0, nkh, c, wsrc, hsrc, esrc, dyn);
+    mlp_step_copies<T, SW, SX>(cur, s, nsteps, c0, nkh, c, wsrc, hsrc, esrc, dyn);
 }
 
 __device__ __forceinline__ CostSplit mlp_shape(const MlpDmaArgs& a) {
@@ -346,10 +343,10 @@ struct MlpSegment {
 // A piece's sources and the ring prologue (the copies of the emulated steps
 // 1 - SW .. -1).  Issued apart from the piece's loop so that a workgroup's
 // first copies leave before any set-up of its own.
-template <int TG, int NTE, bool PAIRED, int SW, int SX, int WMAP>
+template <int TG, int NTE, int SW, int SX, int WMAP>
 __device__ __forceinline__ void mlp_piece_begin(const MlpDmaArgs& a, int item, int c0, int c1, unsigned char* dyn,
-                                                MlpSegment<TG, MlpDmaTraits<TG, NTE, PAIRED, SW, SX>::XPW_E>& sg) {
-    using T = MlpDmaTraits<TG, NTE, PAIRED, SW, SX>;
+                                                MlpSegment<TG, MlpDmaTraits<TG, NTE, SW, SX>::XPW_E>& sg) {
+    using T = MlpDmaTraits<TG, NTE, SW, SX>;
     const int lane = threadIdx.x & 63;
     const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // this wave's quarter of every chunk
     // this lane's row and physical slot in a 1 KiB DMA block of 128-byte rows
@@ -369,20 +366,13 @@ __device__ __forceinline__ void mlp_piece_begin(const MlpDmaArgs& a, int item, i
 #pragma unroll
     for (int v = 0; v < T::XPW_E; ++v) {
         const int q = c + 4 * v;
-        int row, ps;
-        if constexpr (PAIRED) {
-            row = 4 * q + (lane >> 4);
-            ps = (lane & 15) ^ T::swz256(row);
-        } else {
-            row = 8 * q + lrow;
-            ps = lslot ^ T::swz128(row);
-        }
-        sg.esrc[v] = a.xe + (size_t)min(row, a.Re - 1) * a.lde + 8 * ps + (long)(PAIRED ? 128 : 64) * ce0;
+        const int row = 8 * q + lrow, ps = lslot ^ T::swz128(row);
+        sg.esrc[v] = a.xe + (size_t)min(row, a.Re - 1) * a.lde + 8 * ps + 64l * ce0;
     }
     sg.cur = MlpCursor{0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int s = 1 - SW; s < 0; ++s)
-        mlp_step_copies<T, SW, SX, PAIRED>(sg.cur, s, sg.nsteps, c0, a.nkh, c, sg.wsrc, sg.hsrc, sg.esrc, dyn);
+        mlp_step_copies<T, SW, SX>(sg.cur, s, sg.nsteps, c0, a.nkh, c, sg.wsrc, sg.hsrc, sg.esrc, dyn);
 }
 
 // The rest of the piece begun by mlp_piece_begin, streamed through the rings
@@ -390,11 +380,11 @@ __device__ __forceinline__ void mlp_piece_begin(const MlpDmaArgs& a, int item, i
 // hold this thread's part of the piece's sums, the waves' accumulators added
 // in wave order: hc[i] is the 16-byte group 4 tid + 1024 i of [TG][1024] (h
 // phase), ec[i] that of [TG][NTE][1024] (e phase).
-template <int TG, int NTE, bool PAIRED, int SW, int SX>
+template <int TG, int NTE, int SW, int SX>
 __device__ __forceinline__ void mlp_piece_run(const MlpDmaArgs& a,
-                                              MlpSegment<TG, MlpDmaTraits<TG, NTE, PAIRED, SW, SX>::XPW_E>& sg,
+                                              MlpSegment<TG, MlpDmaTraits<TG, NTE, SW, SX>::XPW_E>& sg,
                                               unsigned char* dyn, f32x4 (&hc)[TG], f32x4 (&ec)[TG * NTE]) {
-    using T = MlpDmaTraits<TG, NTE, PAIRED, SW, SX>;
+    using T = MlpDmaTraits<TG, NTE, SW, SX>;
     constexpr int TW = T::TW, NTW = T::NTW;
     static_assert(SX == 2 || SX == 3, "one or two activation chunks in flight");
     const int tid = threadIdx.x;
@@ -425,7 +415,7 @@ __device__ __forceinline__ void mlp_piece_run(const MlpDmaArgs& a,
     // s - 1 are free), then refills the freed stages.
     const int nh = max(0, min(nsteps, a.nkh - c0));   // h-phase chunks of the segment
     for (int s = 0; s < nh; ++s) {
-        mlp_step_begin<T, SW, SX, PAIRED>(cur, s, nsteps, c0, a.nkh, wave, wsrc, sg.hsrc, esrc, dyn);
+        mlp_step_begin<T, SW, SX>(cur, s, nsteps, c0, a.nkh, wave, wsrc, sg.hsrc, esrc, dyn);
         const unsigned char* wt = dyn + cur.rw * T::WSTAGE + wa * TW * T::WTILE;
         const unsigned char* xt = dyn + T::XOFF + cur.rx * T::XSTAGE;
         cur.rw = cur.rw + 1 == SW ? 0 : cur.rw + 1;
@@ -444,7 +434,7 @@ __device__ __forceinline__ void mlp_piece_run(const MlpDmaArgs& a,
         }
     }
     for (int s = nh; s < nsteps; ++s) {
-        mlp_step_begin<T, SW, SX, PAIRED>(cur, s, nsteps, c0, a.nkh, wave, wsrc, sg.hsrc, esrc, dyn);
+        mlp_step_begin<T, SW, SX>(cur, s, nsteps, c0, a.nkh, wave, wsrc, sg.hsrc, esrc, dyn);
         const unsigned char* wt = dyn + cur.rw * T::WSTAGE + wa * TW * T::WTILE;
         const unsigned char* xt = dyn + T::XOFF + cur.rx * T::XSTAGE;
         cur.rw = cur.rw + 1 == SW ? 0 : cur.rw + 1;
@@ -460,15 +450,11 @@ __device__ __forceinline__ void mlp_piece_run(const MlpDmaArgs& a,
             for (int n = 0; n < NTW; ++n) {
                 const int xr = 32 * (NTE >= 2 ? wb * NTW + n : 0) + fr;
                 const int ls = 2 * q + (lane >> 5);
-                if constexpr (PAIRED)
-                    b[n] = *reinterpret_cast<const u32x4*>(xt + xr * 256 + ((ls ^ T::swz256(xr)) << 4));
-                else
-                    b[n] = *reinterpret_cast<const u32x4*>(xt + xr * 128 + ((ls ^ T::swz128(xr)) << 4));
+                b[n] = *reinterpret_cast<const u32x4*>(xt + xr * 128 + ((ls ^ T::swz128(xr)) << 4));
             }
 #pragma unroll
             for (int t = 0; t < TW; ++t) {
-                // paired: sub-step q takes hi (lanes 0-31) and lo (32-63) of weight slot q
-                const int lw = PAIRED ? q : 2 * q + (lane >> 5);
+                const int lw = 2 * q + (lane >> 5);
                 af[t] = *reinterpret_cast<const u32x4*>(wt + t * T::WTILE + fr * 128 + ((lw ^ T::swz128(fr)) << 4));
             }
 #pragma unroll
@@ -613,10 +599,9 @@ __device__ __forceinline__ void mlp_combine_pieces(const float* partial, int nsl
 
 // Every item piece of this workgroup's range; a cut item is summed by its
 // last piece to arrive, in piece order, then written by the epilogue.
-template <int TG, int NTE, bool PAIRED, int SW, int SX, int WMAP, int EPI>
+template <int TG, int NTE, int SW, int SX, int WMAP, int EPI>
 __global__ __launch_bounds__(256, 1) void mlp_dma_kernel(MlpDmaArgs a) {
-    using T = MlpDmaTraits<TG, NTE, PAIRED, SW, SX>;
-    constexpr bool HASH = !PAIRED;   // the down projection alone has no h phase
+    using T = MlpDmaTraits<TG, NTE, SW, SX>;
     extern __shared__ __align__(16) unsigned char dyn[];
     const int tid = threadIdx.x;
     const CostSplit sh = mlp_shape(a);
@@ -625,7 +610,7 @@ __global__ __launch_bounds__(256, 1) void mlp_dma_kernel(MlpDmaArgs a) {
     const int u_end = unit_start(sh, g + 1);
     int u = unit_start(sh, g);
     MlpSegment<TG, T::XPW_E> sg;
-    if (u < u_end) mlp_piece_begin<TG, NTE, PAIRED, SW, SX, WMAP>(a, u / nk, u % nk, min(nk, u_end - u / nk * nk), dyn, sg);
+    if (u < u_end) mlp_piece_begin<TG, NTE, SW, SX, WMAP>(a, u / nk, u % nk, min(nk, u_end - u / nk * nk), dyn, sg);
     while (u < u_end) {
         const int item = u / nk;
         const int c0 = u - item * nk;
@@ -637,7 +622,7 @@ __global__ __launch_bounds__(256, 1) void mlp_dma_kernel(MlpDmaArgs a) {
         pcs.ph1 = __builtin_amdgcn_readfirstlane(pcs.ph1);
         pcs.pe0 = __builtin_amdgcn_readfirstlane(pcs.pe0);
         f32x4 hc[TG], ec[TG * NTE];
-        mlp_piece_run<TG, NTE, PAIRED, SW, SX>(a, sg, dyn, hc, ec);
+        mlp_piece_run<TG, NTE, SW, SX>(a, sg, dyn, hc, ec);
 
         // ---- a cut item: store this piece; the last to arrive sums them
         float* csc = reinterpret_cast<float*>(dyn);   // [TG][1024] h, then [TG][NTE][1024] e
@@ -661,19 +646,19 @@ __global__ __launch_bounds__(256, 1) void mlp_dma_kernel(MlpDmaArgs a) {
                 // e pieces per batch: three for SwiGLU over four tiles (an item's
                 // e half usually spans three pieces), one for the widest residual
                 // epilogue and for eight tiles (registers), else two
-                constexpr int BE = NTE == 8 ? 1 : (NTE == 4 ? (EPI == kMlpEpiSwiGLU ? 3 : (EPI == kMlpEpiResidual && HASH ? 1 : 2)) : 2);
+                constexpr int BE = NTE == 8 ? 1 : (NTE == 4 ? (EPI == kMlpEpiSwiGLU ? 3 : (EPI == kMlpEpiResidual ? 1 : 2)) : 2);
                 mlp_combine_pieces<TG, NTE, T::PF, BE>(a.partial, 2 * a.G, pcs, csc);
                 __syncthreads();
-                mlp_epilogue<TG, NTE, EPI, HASH>(a, item, MlpLdsSums{csc, csc + T::HC * 256});
+                mlp_epilogue<TG, NTE, EPI>(a, item, MlpLdsSums{csc, csc + T::HC * 256});
             }
         } else {
             // a whole item: its sums are in LDS as the piece left them
-            mlp_epilogue<TG, NTE, EPI, HASH>(a, item, MlpLdsSums{csc, csc + T::HC * 256});
+            mlp_epilogue<TG, NTE, EPI>(a, item, MlpLdsSums{csc, csc + T::HC * 256});
         }
         u = (item + 1) * nk;
         if (u < u_end) {
             __syncthreads();   // the epilogue's LDS use ends before the next item's copies land
-            mlp_piece_begin<TG, NTE, PAIRED, SW, SX, WMAP>(a, item + 1, 0, min(nk, u_end - u), dyn, sg);
+            mlp_piece_begin<TG, NTE, SW, SX, WMAP>(a, item + 1, 0, min(nk, u_end - u), dyn, sg);
         }
     }
 }

@@ -305,18 +305,20 @@ inline TilePlan tile_token_plan(int tokens, int N, int d) { return tile_plan(tok
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// The products of the AR approximator when one row block holds every
-// conditional row (mlp_dma.hpp): items of TG weight tiles over their whole
-// reduction range (an h phase of nkh and an e phase of nke 64-column
-// chunks), dealt out to G workgroups of at least kMlpDmaMinUnits chunks.
-// The input projections take four tiles per item, the down projection (its
-// activation rows twice as long: bf16 hi/lo pairs) two, so that one chunk
-// carries 16 MFMAs per wave and 8-16 KiB of weights: fewer, fatter chunks
-// than with one tile, whose per-chunk barrier and latencies otherwise set
-// the pace.
+// The input projections of the AR approximator for few rows (mlp_dma.hpp):
+// items of TG weight tiles over their whole reduction range (an h phase of nkh
+// and an e phase of nke 64-column chunks), dealt out to G workgroups of at
+// least kMlpDmaMinUnits chunks.  Four tiles per item, so that one chunk carries
+// 16 MFMAs per wave and 16 KiB of weights: fewer, fatter chunks than with one
+// tile, whose per-chunk barrier and latencies otherwise set the pace.
+// The down projection (two tiles per item here before) is faster on the
+// block-tiled kernel, which copies half the activation bytes per weight byte:
+// the approximator at 121 rows, d = I = 4096 66 -> 59 us, 2560 55 -> 46,
+// 91 rows 2560 x 9728 95 -> 82.
 #ifndef TF_MLP_DMA_TG_IN
 #define TF_MLP_DMA_TG_IN 4
 #endif
+// items of two tiles without an h phase: no launch makes them now, the checks of the split cover them
 #ifndef TF_MLP_DMA_TG_DOWN
 #define TF_MLP_DMA_TG_DOWN 2
 #endif
@@ -363,36 +365,28 @@ inline bool mlp_dma_plan_ok(const MlpDmaPlan& p) {
 inline MlpDmaPlan mlp_dma_gate_plan(int rows, int d, int ew, int I, bool swiglu) {
     return mlp_dma_plan(rows, swiglu ? cdiv(I, 16) : cdiv(I, 32), d / 64, ew / 64, TF_MLP_DMA_TG_IN);
 }
-// down projection over the activation's hi/lo pairs (no h phase)
-inline MlpDmaPlan mlp_dma_down_plan(int rows, int d, int I) {
-    return mlp_dma_plan(rows, cdiv(d, 32), 0, I / 64, TF_MLP_DMA_TG_DOWN);
-}
 // the linear approximator W_lin [d, 2d] over [h~ ; e~]
 inline MlpDmaPlan mlp_dma_linear_plan(int rows, int d) {
     return mlp_dma_plan(rows, cdiv(d, 32), d / 64, d / 64, TF_MLP_DMA_TG_IN);
 }
-// One row block holds every conditional row and each plan the path may
-// launch (either gate plan, the down projection, the linear layer) keeps its
-// split in 32-bit arithmetic.
-// 129-256 conditional rows: the input projections on the one-row-block kernel
-// (eight activation tiles), the down projection on the kernel for several
-// row blocks (its activation pairs for eight tiles do not fit the LDS).
-inline bool mlp_dma_gate_applies(bool bf16, int b, int gamma, int R, int d, int I, int ew) {
-    if (!(bf16 && (long long)b * gamma <= kMlpDmaMaxStates && (long long)b * R > kMlpDmaMaxRows &&
-          (long long)b * R <= kMlpDmaMaxGateRows && d % 64 == 0 && I % 64 == 0 && ew % 64 == 0))
+// The input projections of at most 256 rows (bigram rows: 128, beyond that
+// their products are taken per token) on the one-row-block kernel; from 129 rows
+// on only weight matrices of 30 M elements and more, whose stream outweighs what
+// the tiles gain: 241 rows, 4096 x 8192 81 us here / 90 tiled, but 242 rows,
+// 2560 x 5120 61 / 54; 181 rows, the gate alone, 6144 x 4096 66 / 56; at 121 rows
+// 4096 x 8192 59 / 75, 2560 x 5120 46 / 48, 29 rows 2048 x 2048 31 / 30.
+inline bool mlp_dma_gate_applies(bool bf16, int b, int gamma, int R, int d, int I, int ew, int bigram) {
+    if (!(bf16 && (long long)b * gamma <= kMlpDmaMaxStates &&
+          (long long)b * R <= (bigram ? kMlpDmaMaxRows : kMlpDmaMaxGateRows) && d % 64 == 0 && I % 64 == 0 && ew % 64 == 0))
         return false;
+    if (b * R > kMlpDmaMaxRows && (long long)I * (d + ew) < 30000000) return false;
     const int rows = b * R;
     return mlp_dma_plan_ok(mlp_dma_gate_plan(rows, d, ew, I, true)) &&
            mlp_dma_plan_ok(mlp_dma_gate_plan(rows, d, ew, I, false));
 }
-inline bool mlp_dma_applies(bool bf16, int b, int gamma, int R, int d, int I, int ew) {
-    if (!(bf16 && (long long)b * gamma <= kMlpDmaMaxStates && (long long)b * R <= kMlpDmaMaxRows && d % 64 == 0 &&
-          I % 64 == 0 && ew % 64 == 0))
-        return false;
-    const int rows = b * R;
-    return mlp_dma_plan_ok(mlp_dma_gate_plan(rows, d, ew, I, true)) &&
-           mlp_dma_plan_ok(mlp_dma_gate_plan(rows, d, ew, I, false)) && mlp_dma_plan_ok(mlp_dma_down_plan(rows, d, I)) &&
-           mlp_dma_plan_ok(mlp_dma_linear_plan(rows, d));
+inline bool mlp_dma_linear_applies(bool bf16, int b, int gamma, int R, int d) {
+    return bf16 && (long long)b * gamma <= kMlpDmaMaxStates && (long long)b * R <= kMlpDmaMaxRows && d % 64 == 0 &&
+           mlp_dma_plan_ok(mlp_dma_linear_plan(b * R, d));
 }
 
 // Long (row, slice) lists for top-k lists of at least kLongListK entries
@@ -427,8 +421,8 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
     const size_t es = bf16 ? 2 : 4;
     const int rows1 = b * gamma, rows2 = b * R;
     const size_t lm1 = lm_scratch_bytes(rows1, V, d, bf16), lm2 = lm_scratch_bytes(rows2, V, d, bf16);
-    const bool tables = bf16 && bigram && !mlp_dma_applies(true, b, gamma, R, d, I, npre * d) &&
-                        tile_width_ok(d, npre * d, I);
+    const bool gate_dma = tile_width_ok(d, npre * d, I) && mlp_dma_gate_applies(bf16, b, gamma, R, d, I, npre * d, bigram);
+    const bool tables = bf16 && bigram && !gate_dma && tile_width_ok(d, npre * d, I);
     const size_t tokens = (size_t)b * bigram_tokens(gamma, k);
     Workspace w;
     size_t off = 0;
@@ -456,24 +450,15 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
         const size_t ld = 2 * (size_t)I > (size_t)d ? 2 * (size_t)I : (size_t)d;
         hhf = (size_t)rows1 * ld * (rows1 <= kTileSplitRows ? 2 : 1) + (tables ? 2 * tokens * ld : 0);
         size_t nc = 0;
-        if (mlp_dma_applies(bf16, b, gamma, R, d, 64, d)) {
+        if (mlp_dma_linear_applies(bf16, b, gamma, R, d)) {
             const MlpDmaPlan ql = mlp_dma_linear_plan(rows2, d);
             mp = mp > ql.part_floats() ? mp : ql.part_floats();
             nc = ql.items;
         }
-        if (mlp_dma_applies(bf16, b, gamma, R, d, I, npre * d)) {
-            // either the SwiGLU or the SiLU gate plan (the SwiGLU one has more
-            // items), and the down projection
+        if (gate_dma) {
+            // either gate plan (the SwiGLU one has more items)
             const MlpDmaPlan qg = mlp_dma_gate_plan(rows2, d, npre * d, I, true),
-                             qs = mlp_dma_gate_plan(rows2, d, npre * d, I, false), qd = mlp_dma_down_plan(rows2, d, I);
-            const size_t pf[] = {qg.part_floats(), qs.part_floats(), qd.part_floats()};
-            for (size_t x : pf) mp = mp > x ? mp : x;
-            const size_t qc = (size_t)qg.items + qd.items;
-            nc = nc > qc ? nc : qc;
-        }
-        if (!bigram && mlp_dma_gate_applies(bf16, b, gamma, R, d, I, d)) {
-            // either gate plan on the one-row-block kernel
-            const MlpDmaPlan qg = mlp_dma_gate_plan(rows2, d, d, I, true), qs = mlp_dma_gate_plan(rows2, d, d, I, false);
+                             qs = mlp_dma_gate_plan(rows2, d, npre * d, I, false);
             mp = mp > qg.part_floats() ? mp : qg.part_floats();
             mp = mp > qs.part_floats() ? mp : qs.part_floats();
             nc = nc > (size_t)qg.items ? nc : (size_t)qg.items;
