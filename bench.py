@@ -50,7 +50,8 @@ RIDGE = BF16_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)
 PROFILES = os.path.join(ROOT, "profiles")
 # sources that define the LM-head GEMM kernel; counters taken on another
 # version of them say nothing about this one
-KERNEL_SOURCES = ["lmhead.hip", "stream_gemm.hpp", "work.hpp", "plan.hpp", "rows.hpp", "common.hpp", "limits.hpp"]
+KERNEL_SOURCES = ["lmhead.hip", "lmhead_tile.hip", "lm_tile.hpp", "tile_gemm.hpp", "dma.hpp", "stream_gemm.hpp",
+                  "work.hpp", "plan.hpp", "rows.hpp", "common.hpp", "limits.hpp"]
 COPY_BYTES = 1 << 30      # plain copy used to scale the traffic counters
 
 
@@ -63,17 +64,16 @@ def kernel_source_digest() -> str:
 
 
 def lm_kernel_pattern(rows: int, d: int) -> str:
-    """Regex for the bf16 LM-head kernel instance the plan picks for `rows` rows
-    (template arguments: weight tiles per wave, activation tiles, waves, ...):
-    every tile shape goes to the LDS-DMA kernel when d is a multiple of its k
-    step (64; beyond two row blocks in 256-row blocks), else to the
-    register-staged kernel."""
+    """Regex for the bf16 LM-head kernel instance the plan picks for `rows` rows over a
+    vocabulary of more than 65536 tokens: the block-tiled kernel beyond 128 rows, else the
+    LDS-DMA kernel (widths that are a multiple of its k step, 64), the block-tiled kernel
+    above 64 rows and the register-staged one (other widths)."""
     nt = 1 if rows <= 32 else (2 if rows <= 64 else 4)
-    if rows <= 256 and d % 64 == 0:   # 32-row tiles, or the wave grid up to two row blocks
+    if rows > 128:                    # (weight tiles of a wave, row tiles of a wave, ...)
+        return r"lmhead_tile_kernel<\d+, [68], "
+    if d % 64 == 0:                   # 32-row tiles, or the wave grid
         return rf"lmhead_dma_kernel<\d+, {nt}, "
-    if nt == 4 and rows > 128 and d % 64 == 0:    # 256-row blocks
-        return r"lmhead_dma_kernel<\d+, 8, "
-    return rf"lmhead_bf16_kernel<\d+, {nt}, "
+    return r"lmhead_tile_kernel<\d+, 4, " if rows > 64 else rf"lmhead_bf16_kernel<\d+, {nt}, "
 
 
 def traffic_file(workload: str) -> str:
@@ -376,7 +376,7 @@ def summarize_mfma(args):
     print(f"\nKernel `{picks[0]['name']}`; mean over {n} dispatches: {avg[0]:.0f} us at {avg[1]:.3f} GHz, MFMA "
           f"busy {avg[2]:.3f} of SIMD cycles, {avg[3]:.0f} TFLOP/s = {avg[3] / BF16_PEAK_TFLOPS:.3f} of the "
           f"2.5 PF peak (rated at {NOMINAL_GHZ} GHz).  The busy fraction exceeds the FLOP fraction at the "
-          f"measured clock by the padded rows ({-(-(w.rows * w.b) // 128) * 128} computed for {w.rows * w.b}).")
+          f"measured clock by the padded rows ({-(-(w.rows * w.b) // 256) * 256} computed for {w.rows * w.b}).")
 
 
 def make_drafter(w, weights):
