@@ -75,6 +75,25 @@ def test_handoff_matches_oracle(b, V, gamma, M, B, agree):
     check(trees, rng.integers(0, V, b), synthetic_targets(rng, trees, V, agree), gamma)
 
 
+@pytest.mark.parametrize("B", [30, 31, 32, 63, 64, 65, 95, 96, 255, 256, 257, 512])
+def test_handoff_at_the_edges_of_a_workgroup(B):
+    """Around 32 positions a mask workgroup, 64 and 256 nodes a pass of the walk; and parents that no node is."""
+    rng = np.random.default_rng(B)
+    V, gamma, M = 80, 7, 5
+    trees = random_trees(rng, 3, V, gamma, M, B)
+    targets = synthetic_targets(rng, trees, V, 0.9)
+    check(trees, rng.integers(0, V, 3), targets, gamma)
+    t = to_dev(trees)
+    stray = dict(t, parent=t["parent"].clone())
+    stray["parent"][:, B // 2:] = B + 7
+    stray["parent"][1, B // 2:] = -5
+    got = binding.treeflash_accept(stray, torch.tensor(targets).cuda(), gamma)
+    for s, tree in enumerate(trees):
+        n = B // 2   # the walk over the nodes that have a parent
+        w = oracle.acceptance_walk(tree["token"][:n], tree["parent"][:n], targets[s])
+        assert int(got["accept_len"][s]) + 1 == w["tau"] and int(got["bonus"][s]) == w["bonus"]
+
+
 def test_handoff_at_the_largest_budget():
     rng = np.random.default_rng(4095)
     V, gamma, M, B = 200, 6, 8, 4095
