@@ -1,5 +1,6 @@
-"""The approximator's block-tiled products (more rows than the one-row-block
-kernels take, widths that are no multiple of 64, many drafter states) against
+"""The approximator's block-tiled products (the down projection, and the input
+projections of more rows than the one-row-block kernel takes, of widths that are
+no multiple of 64, of many drafter states) against
 plain torch in 64 bits, for every tile shape, with and without split
 reductions, and with the bigram rows' products taken once per token.
 
@@ -112,6 +113,11 @@ def _check(form, w, rows=None):
     ("silu", 6, 7, 20, 1040, 1504),     # the state half in two splits; 4 x 4 in four
     ("swiglu", 16, 16, 8, 4096, 64),    # 2 x 4 in eight splits / 8 x 4
     ("swiglu", 1, 16, 16, 128, 6144),   # 241 rows of one sequence
+    # the input projections on the one-row-block kernel, the down projection here: 17 to 128 rows, with and
+    # without splits, and either side of the size from which 129 to 256 rows keep the one-row-block kernel
+    ("swiglu", 1, 5, 4, 64, 4096), ("silu", 1, 32, 1, 192, 1024), ("swiglu", 1, 5, 8, 2560, 512),
+    ("swiglu", 1, 16, 8, 128, 4160), ("swiglu", 4, 8, 4, 192, 64), ("silu", 2, 8, 9, 1088, 6208),
+    ("swiglu", 1, 16, 16, 2048, 7296), ("swiglu", 1, 16, 16, 2048, 7360),
     ("linear", 16, 16, 8, 96, 0),
     ("linear", 16, 16, 8, 2064, 0),     # 5 x 8 in two splits
     ("linear", 16, 16, 8, 4096, 0),     # 4 x 8
