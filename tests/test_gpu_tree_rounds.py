@@ -10,7 +10,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _walk(idx, lp, topk, gamma, k, B, marginal):
+def _walk(idx, lp, topk, gamma, k, B, marginal, bigram=False):
     """One pop at a time: score desc, depth asc, rank path asc; a node's next sibling follows it into the queue."""
     K2 = idx.shape[1]
     out = []
@@ -33,17 +33,24 @@ def _walk(idx, lp, topk, gamma, k, B, marginal):
                 child = depth
             else:
                 hit = np.nonzero(topk[depth - 1] == tok)[0]
-                if hit.size:
+                if hit.size and bigram and depth > 1:
+                    older = row - 1 if depth == 2 else (row - 1 - k) % k
+                    child = 1 + k + (depth - 2) * k * k + older * k + int(hit[0])
+                elif hit.size:
                     child = 1 + (depth - 1) * k + int(hit[0])
             if child is not None:
                 push(queue, np.float32(s), depth + 1, child, path, 0, n)
     return out
 
 
-def _case(shape, gamma, k, K2, seed, marginal):
+def _case(shape, gamma, k, K2, seed, marginal, bigram=False):
     rng = np.random.default_rng(seed)
     R = gamma if marginal else 1 + (gamma - 1) * k
     depth = np.arange(R) if marginal else np.concatenate([[0], 1 + np.arange((gamma - 1) * k) // k])
+    if bigram:
+        depth = np.concatenate([[0], np.ones(k, int), 2 + np.arange(max(gamma - 2, 0) * k * k) // (k * k)])
+        depth = depth[:1] if gamma == 1 else depth
+        R = len(depth)
     topk = np.stack([rng.permutation(5000)[:k] for _ in range(gamma)])
     idx = np.empty((R, K2), np.int64)
     for r in range(R):   # the depth's candidates lead most rows
@@ -95,6 +102,24 @@ def test_rounds_pop_what_the_walk_pops(shape, gamma, k, K2, B, marginal):
             g = got[name][s].cpu().numpy()
             assert g[:n].tolist() == [w[f] for w in want], f"{name} differs"
         assert (got["token"][s, n:] == -1).all() and (got["depth"][s, n:] == 0).all()
+
+
+# bigram rows: parents of depth 1, 2 and deeper, no and one level of children, rows of which LDS holds a part (905 x 128)
+@pytest.mark.parametrize("shape,gamma,k,K2,B", [
+    ("peaked", 8, 4, 100, 100), ("peaked", 16, 8, 128, 128), ("peaked", 1, 4, 300, 300), ("peaked", 2, 5, 100, 90),
+    ("ties", 6, 4, 80, 80), ("peaked", 5, 12, 256, 512), ("flat", 7, 5, 65, 65), ("unsorted", 8, 4, 100, 100),
+])
+def test_bigram_rounds_pop_what_the_walk_pops(shape, gamma, k, K2, B):
+    import torch
+    from paper_2606_03819_amd import binding
+    cases = [_case(shape, gamma, k, K2, seed, False, bigram=True) for seed in (1, 2)]
+    idx, lp, topk = (torch.from_numpy(np.stack(x)).cuda() for x in zip(*cases))
+    got = binding.treeflash_build_tree_2prev(idx, lp, topk, B)
+    for s, (i, p, t) in enumerate(cases):
+        want = _walk(i, p, t, gamma, k, B, False, bigram=True)
+        assert len(want) == B
+        for f, name in enumerate(("token", "parent", "depth", "score")):
+            assert got[name][s].cpu().numpy().tolist() == [w[f] for w in want], f"{name} differs"
 
 
 def test_rounds_leave_nan_to_the_serial_selection():
