@@ -185,6 +185,8 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
     const uint32_t target = a.B + 1;   // with the root
     // the root alone has B entries: none below the B-th can be among the B best
     const float edge = get_lp(0, min(K2, a.B) - 1);
+    // no such bound: at a threshold above the root's 0, or none, nothing would be taken and nothing checked
+    if (K2 >= a.B && !(edge <= 0.f)) return false;
     float tau = K2 >= a.B ? 0.f + edge : neg_inf();
     float scale = 1000.f / fminf(fmaxf(-edge, 1e-3f), 1e6f);   // bins of the score, finer as tau rises
     int n = 1;

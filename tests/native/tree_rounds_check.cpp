@@ -296,6 +296,18 @@ int main() {
             }
             for (const char* sh : {"ties", "zeros", "allzero", "edge", "impossible"})
                 check(make(mode, s.gamma, s.M, s.K2, s.B, sh), sh, -1);
+            // what the serial selection reads first: the first row's leading entries, up to the B-th
+            for (int at : {0, s.B / 2, s.B - 1}) {
+                if (at >= s.K2) continue;
+                Case c = make(mode, s.gamma, s.M, s.K2, s.B, "peaked");
+                c.lp[at] = NAN;
+                check(c, "nan", 0);
+            }
+            for (int upto : {1, s.K2}) {
+                Case c = make(mode, s.gamma, s.M, s.K2, s.B, "peaked");
+                for (int i = 0; i < upto; ++i) c.lp[i] += 60.f;
+                check(c, "positive", 0);
+            }
             for (int rep = 0; rep < 2; ++rep) {   // any entries out of order, positive or not
                 Case c = make(mode, s.gamma, s.M, s.K2, s.B, "peaked");
                 for (int i = 0; i < 1 + 4 * rep; ++i) c.lp[rng() % c.lp.size()] = uniform(-2.f, rep ? 1.f : 0.f);

@@ -133,3 +133,28 @@ def test_rounds_leave_nan_to_the_serial_selection():
         small, large = (binding.treeflash_build_tree(idx, lp, topk, B) for B in (64, 100))
         for f in ("token", "parent", "depth"):
             assert torch.equal(small[f], large[f][:, :64]), f
+
+
+@pytest.mark.parametrize("B", [65, 100, 300, 512])
+@pytest.mark.parametrize("marginal", [False, True])
+def test_a_first_row_out_of_order_up_to_its_last_entry(B, marginal):
+    """The first row's B-th entry bounds the tree: NaN or positive there (every entry positive), it must not."""
+    import torch
+    from paper_2606_03819_amd import binding
+    i, p, t = _case("peaked", 8, 4, B, 3, marginal)
+
+    def build(lp, budget):
+        idx, row, topk = (torch.from_numpy(x[None]).cuda() for x in (i, lp, t))
+        got = (binding.treeflash_build_tree_marginal(idx, row, budget) if marginal
+               else binding.treeflash_build_tree(idx, row, topk, budget))
+        return {f: got[f][0].cpu().numpy() for f in ("token", "parent", "depth", "score")}
+    positive = p.copy()
+    positive[0] += np.float32(60)
+    got, want = build(positive, B), _walk(i, positive, t, 8, 4, B, marginal)
+    for f, name in enumerate(got):
+        assert got[name].tolist() == [w[f] for w in want], name
+    nan = p.copy()
+    nan[0, B - 1] = np.nan
+    large, small = build(nan, B), build(nan, 64)   # 64 nodes are always selected serially
+    for name in ("token", "parent", "depth"):
+        assert large[name][:64].tolist() == small[name].tolist() and (large["depth"] > 0).all(), name
