@@ -65,6 +65,8 @@ typedef enum { TF_F32 = 0, TF_BF16 = 1 } tf_dtype_t;
 
 /* Bytes of device workspace the two Part-1 calls need for these shapes (the
  * larger of the two).  `topk2` is the stage-2 list length (see below).
+ * For the same d, I, V and dt the size never falls as b, gamma or k grow, so a
+ * workspace made for the largest call serves every smaller one.
  * Returns 0 if the shapes are invalid.  The first 64 bytes of the workspace
  * hold diagnostic counters: int32 at byte offset 0 counts the (row, vocabulary
  * slice) pairs the last call re-evaluated on its exact slow path. */
@@ -235,7 +237,8 @@ tf_status_t treeflash_build_tree(const int32_t *cond_idx, const float *cond_logp
 
 /* Workspace bytes of treeflash_arapprox_2prev_hidden and of the LM-head call
  * on its rows (treeflash_marginal_topk on h' viewed as [b, R2, d] with k =
- * topk2); 0 for invalid shapes. */
+ * topk2); 0 for invalid shapes.  As above, a larger b, gamma or k never needs
+ * less. */
 size_t treeflash_workspace_bytes_2prev(int b, int gamma, int d, int I, int V, int k, int topk2,
                                        tf_dtype_t dt);
 

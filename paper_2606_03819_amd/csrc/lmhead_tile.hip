@@ -85,23 +85,8 @@ hipError_t launch_lm_tile(const LmPlan& p, const uint16_t* x, long ldx, const ui
     const LmTileArgs a{x, ldx, w, rows, d, V, p.nrb, p.nsplit(), p.map, sl2, part, diag};
     const int nb = p.blocks();
 #define TF_LM_TILE_CASE(WMT, NXT, WNT) \
-    if (p.WM == WMT && p.NT == NXT && p.wnt == WNT) return launch_shape<WMT, NXT, WNT>(a, nb, longl, st)
-    TF_LM_TILE_CASE(8, 8, false);
-    TF_LM_TILE_CASE(8, 6, false);
-    TF_LM_TILE_CASE(8, 8, true);
-    TF_LM_TILE_CASE(7, 8, true);
-    TF_LM_TILE_CASE(6, 8, true);
-    TF_LM_TILE_CASE(8, 6, true);
-    TF_LM_TILE_CASE(7, 6, true);
-    TF_LM_TILE_CASE(6, 6, true);
-    TF_LM_TILE_CASE(8, 4, true);
-    TF_LM_TILE_CASE(7, 4, true);
-    TF_LM_TILE_CASE(6, 4, true);
-    TF_LM_TILE_CASE(4, 4, true);
-    TF_LM_TILE_CASE(8, 2, true);
-    TF_LM_TILE_CASE(7, 2, true);
-    TF_LM_TILE_CASE(6, 2, true);
-    TF_LM_TILE_CASE(4, 2, true);
+    if (p.WM == WMT && p.NT == NXT && p.wnt == WNT) return launch_shape<WMT, NXT, WNT>(a, nb, longl, st);
+    TF_LM_TILE_SHAPES(TF_LM_TILE_CASE)
 #undef TF_LM_TILE_CASE
     return hipErrorInvalidValue;
 }

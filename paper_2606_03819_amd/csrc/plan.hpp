@@ -3,6 +3,8 @@
 // workspace size the caller is told and the layout the kernels use agree.
 #pragma once
 
+#include <initializer_list>
+
 #include <stddef.h>
 #include <stdint.h>
 
@@ -34,6 +36,7 @@ constexpr int kNumCUs = 256;           // compute units of an MI355X
 #endif
 
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
+inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 inline int plan_nt(int rows) { return rows <= 32 ? 1 : (rows <= 64 ? 2 : 4); }
 
@@ -122,6 +125,12 @@ inline int lm_wm(int NT) { return NT == 1 ? TF_LM_WM_NT1 : (NT == 2 ? TF_LM_WM_N
 // 233 / 247; width 2000: 121 x 100000 149 / 131, 48 x 151936 199 / 204.
 constexpr int kTileMinRows = 129;
 constexpr int kTileMaxK = 1 << 20;
+
+// Tile shapes (WM, NT, one row block).
+#define TF_LM_TILE_SHAPES(F)                                                                               \
+    F(8, 8, false) F(8, 6, false) F(8, 8, true) F(7, 8, true) F(6, 8, true) F(8, 6, true) F(7, 6, true)    \
+    F(6, 6, true) F(8, 4, true) F(7, 4, true) F(6, 4, true) F(4, 4, true) F(8, 2, true) F(7, 2, true)      \
+    F(6, 2, true) F(4, 2, true)
 
 // Row blocks of at most 256 rows, 192 where the rows then fill them (a wave
 // grid of 2 x 2 waves of 16-row tiles: NXT = 8 or 6; 4 and 2 for up to 128 and
@@ -234,9 +243,9 @@ constexpr int kTileSplitFloats = 16384;    // most fp32 partial sums of a row, o
 constexpr int kTileSplitRows = 2048;       // rows up to which products are split (more rows make tiles enough)
 constexpr int kTileMinSteps = 4;           // fewest steps of a split
 
-// Partial sums a row's split products may take (floats): grows with N.
+// Partial sums a row's split products may take (floats); none once two splits pass the limit.
 inline long long tile_split_floats(int rows, long long N) {
-    if (rows > kTileSplitRows) return 0;
+    if (rows > kTileSplitRows || 2 * N > kTileSplitFloats) return 0;
     return N * kTileSplits < kTileSplitFloats ? N * kTileSplits : kTileSplitFloats;
 }
 
@@ -302,8 +311,6 @@ inline TilePlan tile_input_plan(int rows, int N, int ew) {
 inline TilePlan tile_down_plan(int rows, int d, int I) { return tile_plan(rows, d, I, 1, true, kTileSplits, false); }
 // the bigram rows' products, once per state and previous token
 inline TilePlan tile_token_plan(int tokens, int N, int d) { return tile_plan(tokens, N, d, 3, false, 1, true); }
-
-inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The input projections of the AR approximator for few rows (mlp_dma.hpp):
 // items of TG weight tiles over their whole reduction range (an h phase of nkh
@@ -375,18 +382,20 @@ inline MlpDmaPlan mlp_dma_linear_plan(int rows, int d) {
 // the tiles gain: 241 rows, 4096 x 8192 81 us here / 90 tiled, but 242 rows,
 // 2560 x 5120 61 / 54; 181 rows, the gate alone, 6144 x 4096 66 / 56; at 121 rows
 // 4096 x 8192 59 / 75, 2560 x 5120 46 / 48, 29 rows 2048 x 2048 31 / 30.
+inline bool mlp_dma_gate_rows(long long rows, int d, int I, int ew, int bigram) {
+    if (rows > (bigram ? kMlpDmaMaxRows : kMlpDmaMaxGateRows) || d % 64 != 0 || I % 64 != 0 || ew % 64 != 0) return false;
+    if (rows > kMlpDmaMaxRows && (long long)I * (d + ew) < 30000000) return false;
+    return mlp_dma_plan_ok(mlp_dma_gate_plan((int)rows, d, ew, I, true)) &&
+           mlp_dma_plan_ok(mlp_dma_gate_plan((int)rows, d, ew, I, false));
+}
 inline bool mlp_dma_gate_applies(bool bf16, int b, int gamma, int R, int d, int I, int ew, int bigram) {
-    if (!(bf16 && (long long)b * gamma <= kMlpDmaMaxStates &&
-          (long long)b * R <= (bigram ? kMlpDmaMaxRows : kMlpDmaMaxGateRows) && d % 64 == 0 && I % 64 == 0 && ew % 64 == 0))
-        return false;
-    if (b * R > kMlpDmaMaxRows && (long long)I * (d + ew) < 30000000) return false;
-    const int rows = b * R;
-    return mlp_dma_plan_ok(mlp_dma_gate_plan(rows, d, ew, I, true)) &&
-           mlp_dma_plan_ok(mlp_dma_gate_plan(rows, d, ew, I, false));
+    return bf16 && (long long)b * gamma <= kMlpDmaMaxStates && mlp_dma_gate_rows((long long)b * R, d, I, ew, bigram);
+}
+inline bool mlp_dma_linear_rows(long long rows, int d) {
+    return rows <= kMlpDmaMaxRows && d % 64 == 0 && mlp_dma_plan_ok(mlp_dma_linear_plan((int)rows, d));
 }
 inline bool mlp_dma_linear_applies(bool bf16, int b, int gamma, int R, int d) {
-    return bf16 && (long long)b * gamma <= kMlpDmaMaxStates && (long long)b * R <= kMlpDmaMaxRows && d % 64 == 0 &&
-           mlp_dma_plan_ok(mlp_dma_linear_plan(b * R, d));
+    return bf16 && (long long)b * gamma <= kMlpDmaMaxStates && mlp_dma_linear_rows((long long)b * R, d);
 }
 
 // Long (row, slice) lists for top-k lists of at least kLongListK entries
@@ -405,68 +414,93 @@ inline size_t lm_scratch_bytes(int rows, int V, int d, bool bf16) {
     return lm_scratch_bytes(lm_plan(rows, V, d, bf16), rows, bf16);
 }
 
+// LM-head scratch that serves every call of up to `rows` rows.  bf16: the slices
+// of a row change only at these row counts, not always upwards (129 to 256 rows
+// may take more than 257).  fp32: slices of one tile shrink in number as more row
+// blocks come, and are then at most 512 a row block and one a row more.
+inline size_t lm_reserve_bytes(int rows, int V, int d, bool bf16) {
+    size_t most = lm_scratch_bytes(rows, V, d, bf16);
+    if (bf16) {
+        for (int r : {32, 64, 128, 192, 256})
+            if (r < rows && lm_scratch_bytes(r, V, d, bf16) > most) most = lm_scratch_bytes(r, V, d, bf16);
+        return most;
+    }
+    const long long tiles = cdiv(V, 32), one = (long long)rows * tiles, few = 2ll * kNumCUs * 16 + cdiv(rows, 16) * 16;
+    const long long parts = (long long)rows * cdiv(tiles, 8), fine = one < few ? one : few;
+    return align256((size_t)(parts > fine ? parts : fine) * kPartStride * 4);
+}
+
 struct Workspace {
     size_t diag, lm, ht, et, act, hp, mlp_part, counters, hh, total;
     int ncounters;
 };
 
-// Layout: [diag counters | LM-head scratch (stage 1 or stage 2) | normalised
-// h | normalised embeddings | SwiGLU activation | h' | SwiGLU partial sums |
-// SwiGLU arrival counters | h~-half table of the split input projections].
-// Stage 1 uses the first two only.  `bigram` sizes the w/ 2-prev rows (two
-// embeddings per row, a 3d-wide input).
+// Layout: [diag counters | LM-head scratch (stage 1 or stage 2), or before it the
+// approximator's partial sums | normalised h | normalised embeddings | SwiGLU
+// activation | h' | SwiGLU arrival counters | h~-half table of the split input
+// projections].  Stage 1 uses the first two only.  `bigram` sizes the w/ 2-prev
+// rows (two embeddings per row, a 3d-wide input).
+//
+// No part shrinks as b, gamma or k grow, so that a workspace made for the largest
+// call serves the smaller ones: where a plan needs more at fewer rows (pieces of
+// the one-row-block kernel, splits of products that have too few tiles), its most
+// is reserved from there on.  Nor is the whole ever smaller than at I = 16, which
+// the linear layer, whatever I the workspace was sized with, asks for.
 inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, bool bf16, bool bigram = false) {
     const int R = (int)cond_rows(gamma, k, bigram ? 1 : 0);
     const int npre = bigram ? 2 : 1;
     const size_t es = bf16 ? 2 : 4;
-    const int rows1 = b * gamma, rows2 = b * R;
-    const size_t lm1 = lm_scratch_bytes(rows1, V, d, bf16), lm2 = lm_scratch_bytes(rows2, V, d, bf16);
-    const bool gate_dma = tile_width_ok(d, npre * d, I) && mlp_dma_gate_applies(bf16, b, gamma, R, d, I, npre * d, bigram);
-    const bool tables = bf16 && bigram && !gate_dma && tile_width_ok(d, npre * d, I);
+    const int rows1 = b * gamma, rows2 = b * R;   // R >= gamma
     const size_t tokens = (size_t)b * bigram_tokens(gamma, k);
+    const bool tables = bf16 && bigram && tile_width_ok(d, npre * d, I);
+    size_t mp = 0, hhf = 0, erows = (size_t)rows2 * npre;
     Workspace w;
+    w.ncounters = 0;
+    if (bf16) {
+        // split products: at most kTileSplitFloats a row, of at most kTileSplitRows rows
+        const int rs = rows2 < kTileSplitRows ? rows2 : kTileSplitRows;
+        for (const long long N : {2ll * I, (long long)I, (long long)d}) {
+            const size_t f = (size_t)rs * tile_split_floats(rs, N);
+            mp = mp > f ? mp : f;
+            // the h~ tables: two splits of up to kTileSplitRows states, one of more
+            const long long two = tile_split_floats(1, N) > 0 ? 2ll * (rows1 < kTileSplitRows ? rows1 : kTileSplitRows) : 0;
+            const size_t hf = (size_t)N * (rows1 > two ? rows1 : two);
+            hhf = hhf > hf ? hhf : hf;
+        }
+        if (tables) {
+            const size_t ld = 2 * (size_t)I > (size_t)d ? 2 * (size_t)I : (size_t)d;
+            hhf += 2 * tokens * ld;
+            const size_t few = (size_t)(rows2 < kMlpDmaMaxRows ? rows2 : kMlpDmaMaxRows) * npre;
+            erows = tokens > few ? tokens : few;
+        }
+        // the one-row-block kernel at each number of activation tiles up to this call's
+        for (int r = 32; r <= kMlpDmaMaxGateRows && (r == 32 || r / 2 < rows2); r *= 2) {
+            const int n = r < rows2 ? r : rows2;
+            auto need = [&](const MlpDmaPlan& q) {
+                mp = mp > q.part_floats() ? mp : q.part_floats();
+                w.ncounters = w.ncounters > q.items ? w.ncounters : q.items;
+            };
+            if (mlp_dma_linear_rows(n, d)) need(mlp_dma_linear_plan(n, d));
+            if (tile_width_ok(d, npre * d, I) && mlp_dma_gate_rows(n, d, I, npre * d, bigram)) {
+                need(mlp_dma_gate_plan(n, d, npre * d, I, true));
+                need(mlp_dma_gate_plan(n, d, npre * d, I, false));
+            }
+        }
+    }
+    const size_t lm = lm_reserve_bytes(rows2, V, d, bf16), part = align256(mp * 4);
     size_t off = 0;
     w.diag = off;
     off += 256;
-    w.lm = off;
-    off += lm1 > lm2 ? lm1 : lm2;
+    w.lm = w.mlp_part = off;   // the LM head reads h' only once the partial sums are finished
+    off += lm > part ? lm : part;
     w.ht = off;
     off += align256((size_t)rows1 * d * es);
     w.et = off;
-    off += align256((tables ? tokens : (size_t)rows2 * npre) * d * es);
+    off += align256(erows * d * es);
     w.act = off;
     off += align256((size_t)rows2 * I * es * (bf16 ? 2 : 1));   // bf16: hi/lo pairs
     w.hp = off;
     off += align256((size_t)rows2 * d * es);
-    size_t mp = 0;
-    w.ncounters = 0;
-    size_t hhf = 0;
-    if (bf16) {
-        // The linear layer asks for this layout at the smallest I, whatever
-        // I the workspace was sized with: its needs are part of every layout,
-        // and no term shrinks as I grows.
-        const long long gf = tile_split_floats(rows2, 2ll * I), df = tile_split_floats(rows2, d);
-        mp = (size_t)rows2 * (gf > df ? gf : df);
-        const size_t ld = 2 * (size_t)I > (size_t)d ? 2 * (size_t)I : (size_t)d;
-        hhf = (size_t)rows1 * ld * (rows1 <= kTileSplitRows ? 2 : 1) + (tables ? 2 * tokens * ld : 0);
-        size_t nc = 0;
-        if (mlp_dma_linear_applies(bf16, b, gamma, R, d)) {
-            const MlpDmaPlan ql = mlp_dma_linear_plan(rows2, d);
-            mp = mp > ql.part_floats() ? mp : ql.part_floats();
-            nc = ql.items;
-        }
-        if (gate_dma) {
-            // either gate plan (the SwiGLU one has more items)
-            const MlpDmaPlan qg = mlp_dma_gate_plan(rows2, d, npre * d, I, true),
-                             qs = mlp_dma_gate_plan(rows2, d, npre * d, I, false);
-            mp = mp > qg.part_floats() ? mp : qg.part_floats();
-            mp = mp > qs.part_floats() ? mp : qs.part_floats();
-            nc = nc > (size_t)qg.items ? nc : (size_t)qg.items;
-        }
-        w.ncounters = (int)nc;
-    }
-    w.mlp_part = off;
-    off += align256(mp * 4);
     w.counters = off;
     off += align256((size_t)w.ncounters * 4);
     w.hh = off;

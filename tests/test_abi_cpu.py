@@ -150,6 +150,18 @@ def test_arapprox_linear_hidden_rejects(over, code):
     assert _linear(**over) == code
 
 
+@pytest.mark.parametrize("d,I", [(4096, 4096), (2560, 2560), (2560, 9728), (2000, 3008)])
+def test_workspace_of_a_larger_call_serves_the_smaller_ones(d, I):
+    f, f2 = binding.lib().treeflash_workspace_bytes, binding.lib().treeflash_workspace_bytes_2prev
+    for size, most in ((f, 40), (f2, 6)):
+        for dt in (BF16, F32):
+            by_b = [size(b, 16, d, I, 151936, 8, 32, dt) for b in range(1, most)]
+            by_gamma = [size(1, gamma, d, I, 151936, 8, 32, dt) for gamma in range(1, 60)]
+            by_k = [size(2, 16, d, I, 151936, k, 32, dt) for k in range(1, 40)]
+            for sizes in (by_b, by_gamma, by_k):
+                assert sizes[0] > 0 and sizes == sorted(sizes)
+
+
 def test_linear_workspace_fits_in_the_swiglu_one():
     # the linear variant's workspace (any SwiGLU width stands in) never exceeds
     # what treeflash_workspace_bytes gives for the smallest width
