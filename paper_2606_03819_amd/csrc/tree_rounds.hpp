@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "plan.hpp"
+
 namespace tf {
 
 constexpr int kTreeThreads = 1024;  // all waves preload; wave 0 alone selects
@@ -71,9 +73,11 @@ inline size_t pool_lds_bytes(int Rs, int K2, int ncand) {
     return kPoolFixed + (size_t)4 * ncand + (size_t)4 * Rs * pool_ranks(Rs, K2, ncand);
 }
 
-// Selection in rounds from 65 to 512 nodes.  One sequence, us, serial / rounds: peaked rows, 32 nodes 17 / 26, 48
-// 25 / 34, 64 32 / 31, 66 43 / 37, 96 62 / 42, 128 82 / 45, 512 789 / 97; star-shaped trees (sibling runs in the
-// serial one), 100 nodes 9.5 / 9.6, 256 15 / 11, 512 30 / 17.
+// Selection in rounds from 65 to 512 nodes.  One sequence of 121 rows, us, serial / rounds: peaked rows, 32 nodes
+// 17 / 26, 48 25 / 34, 64 32 / 31, 65 43 / 31, 96 63 / 40, 128 83 / 46, 256 256 / 48, 512 789 / 81; star-shaped trees,
+// 65 nodes 5.1 / 9.4, 128 7.1 / 10.6, 256 16 / 13, 512 30 / 21; rows of fewer entries than
+// nodes, peaked, 32 entries and 128 nodes 81 / 49, 16 and 256 202 / 57.  Flat rows one entry short of the budget are
+// the worst left: 64 and 65 5.1 / 13.7.
 constexpr int kPoolMinBudget = 65, kPoolMaxBudget = 512;
 inline bool tree_takes_rounds(int B, int Rs, int K2, int ncand) {
     return B >= kPoolMinBudget && B <= kPoolMaxBudget && pool_ranks(Rs, K2, ncand) >= 1 && Rs < 65535;
@@ -132,6 +136,8 @@ __device__ inline bool pool_tie_before(const Pool& p, int x, int y) {
     return (lx & 0xffff) < (ly & 0xffff);
 }
 
+static_assert(kMaxTopk <= kTreeThreads, "a thread a row of depth 2");
+
 // Selects a sequence's tree; false (for the whole workgroup, nothing written)
 // when the rows or their ties call for the serial selection.
 __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
@@ -189,6 +195,9 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
     if (K2 >= a.B && !(edge <= 0.f)) return false;
     float tau = K2 >= a.B ? 0.f + edge : neg_inf();
     float scale = 1000.f / fminf(fmaxf(-edge, 1e-3f), 1e6f);   // bins of the score, finer as tau rises
+    // rows of fewer than B entries do not bound the B-th best, which lies rows deeper: left out of the bins it leaves
+    // the threshold open, and the pool overflows with nodes of no use
+    if (K2 < a.B) scale *= 0.0625f;
     int n = 1;
     bool packed = false;
     uint32_t total;
@@ -356,6 +365,8 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
             const float t = -((float)(bin + 1) / scale) * 1.000001f;
             tau = fmaxf(tau, t);
             if (tau < 0.f) scale = fminf(1000.f / -tau, 1e30f);
+        } else if (total >= target) {
+            scale *= 0.0625f;   // the B-th best lies past the bins
         }
     }
 

@@ -283,7 +283,8 @@ static void check(const Case& c, const char* shape, int want) {
 int main() {
     struct { int gamma, M, K2, B; } sizes[] = {
         {16, 8, 256, 256}, {16, 8, 65, 65}, {9, 3, 40, 512}, {16, 30, 128, 128}, {1, 4, 300, 300}, {2, 5, 100, 90},
-        {3, 2, 30, 150}, {12, 16, 300, 300}, {16, 8, 512, 400}, {5, 4, 512, 512}, {8, 4, 4096, 100}};
+        {3, 2, 30, 150}, {12, 16, 300, 300}, {16, 8, 512, 400}, {5, 4, 512, 512}, {8, 4, 4096, 100}, {16, 8, 16, 256},
+        {16, 8, 32, 65}, {16, 8, 32, 512}};
     for (auto s : sizes)
         for (int mode : {kTreeSingle, kTreeMarginal, kTreeBigram}) {
             if (mode == kTreeBigram && s.M > 16) continue;
@@ -292,7 +293,7 @@ int main() {
             if (cap < s.B) continue;
             for (const char* sh : {"peaked", "flat", "mixed", "tail"}) {
                 // rows of fewer than B entries give no threshold to start from, and may overflow the pool
-                check(make(mode, s.gamma, s.M, s.K2, s.B, sh), sh, s.K2 >= s.B && sh[0] != 't' ? 1 : -1);
+                check(make(mode, s.gamma, s.M, s.K2, s.B, sh), sh, sh[0] != 't' ? 1 : -1);
             }
             for (const char* sh : {"ties", "zeros", "allzero", "edge", "impossible"})
                 check(make(mode, s.gamma, s.M, s.K2, s.B, sh), sh, -1);
