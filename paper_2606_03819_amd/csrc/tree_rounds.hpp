@@ -75,7 +75,7 @@ inline size_t pool_lds_bytes(int Rs, int K2, int ncand) {
 
 // Selection in rounds from 65 to 512 nodes.  One sequence of 121 rows, us, serial / rounds: peaked rows, 32 nodes
 // 17 / 26, 48 25 / 34, 64 32 / 31, 65 43 / 31, 96 63 / 40, 128 83 / 46, 256 256 / 48, 512 789 / 81; star-shaped trees,
-// 65 nodes 5.1 / 9.4, 128 7.1 / 10.6, 256 16 / 13, 512 30 / 21; rows of fewer entries than
+// 65 nodes 5.1 / 3.3, 128 7.1 / 3.8, 256 16 / 4.8, 512 (not all of a row staged) 30 / 21; rows of fewer entries than
 // nodes, peaked, 32 entries and 128 nodes 81 / 49, 16 and 256 202 / 57.  Flat rows one entry short of the budget are
 // the worst left: 64 and 65 5.1 / 13.7.
 constexpr int kPoolMinBudget = 65, kPoolMaxBudget = 512;
@@ -92,7 +92,7 @@ struct Pool {
     uint32_t* bins;    // histogram; reused for the renumbering
     uint16_t* place;
     uint32_t* tot;     // 3 x 16 wave totals
-    int* word;         // [0] pool size, [1] bin, [2] rows in order so far, [3] nodes to expand
+    int* word;         // [0] pool size, [1] bin, [2] rows in order so far, [3] nodes to expand, [4] no star
     int* tk;
     float* lp;         // [Rs][P]
 };
@@ -168,6 +168,7 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
         p.word[0] = 1;
         p.word[2] = 1;
         p.word[3] = 0;
+        p.word[4] = 0;
         p.score[0] = 0.f;   // the root: entry 0
         p.link[0] = 0;
         p.info[0] = (1u << 16) | kSeen;
@@ -194,6 +195,30 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
     // no such bound: at a threshold above the root's 0, or none, nothing would be taken and nothing checked
     if (K2 >= a.B && !(edge <= 0.f)) return false;
     float tau = K2 >= a.B ? 0.f + edge : neg_inf();
+    // A star-shaped tree: no row that a first pop could open starts above the first row's B-th entry, so that row's
+    // first B entries are the tree (flat rows, as random weights make them).  Looked for where the staged ranks show
+    // it; the serial selection takes such trees in a few sibling runs, and the rounds took twice as long.
+    if (P >= a.B) {
+        const int below = a.gamma < 2 ? 0 : a.mode == kTreeMarginal ? 1 : a.M;   // rows of depth 2: 1 ..
+        const bool sorted = tid >= a.B || p.lp[tid] <= (tid > 0 ? p.lp[tid - 1] : 0.f);
+        if (!sorted || (tid < below && !(0.f + p.lp[0] + p.lp[(1 + tid) * P] < tau))) p.word[4] = 1;
+        __syncthreads();
+        if (p.word[4] == 0) {
+            if (tid < a.B) {
+                const int tok = ridx[tid];
+                int crow = a.mode == kTreeMarginal && below > 0 ? 1 : -1;
+                if (a.mode != kTreeMarginal)
+                    for (int m = below - 1; m >= 0; --m) crow = p.tk[m] == tok ? 1 + m : crow;
+                const size_t o = (size_t)seq * a.B + tid;
+                a.tok[o] = tok;
+                a.par[o] = -1;
+                a.dep[o] = 1;
+                a.score[o] = 0.f + p.lp[tid];
+                if (a.crow != nullptr) a.crow[o] = crow;
+            }
+            return true;
+        }
+    }
     float scale = 1000.f / fminf(fmaxf(-edge, 1e-3f), 1e6f);   // bins of the score, finer as tau rises
     // rows of fewer than B entries do not bound the B-th best, which lies rows deeper: left out of the bins it leaves
     // the threshold open, and the pool overflows with nodes of no use

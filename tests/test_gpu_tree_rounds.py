@@ -82,6 +82,8 @@ def _case(shape, gamma, k, K2, seed, marginal, bigram=False):
     ("peaked", 1, 4, 300, 300), ("peaked", 3, 2, 30, 150), ("peaked", 12, 16, 300, 300), ("peaked", 16, 8, 512, 400),
     ("flat", 16, 8, 256, 256), ("ties", 8, 4, 100, 100), ("ties", 16, 8, 256, 512), ("zeros", 6, 4, 80, 80),
     ("peaked", 16, 8, 16, 256), ("flat", 16, 8, 32, 128), ("peaked", 16, 8, 32, 512), ("flat", 4, 8, 64, 65),
+    # star-shaped trees: the first row's entries alone
+    ("flat", 16, 8, 65, 65), ("flat", 16, 8, 128, 128), ("flat", 1, 4, 100, 100), ("flat", 12, 40, 200, 130),
     ("tail", 6, 4, 100, 300), ("unsorted", 8, 4, 100, 100), ("positive", 8, 4, 100, 100), ("unsorted", 16, 20, 70, 70),
 ])
 @pytest.mark.parametrize("marginal", [False, True])
