@@ -165,6 +165,12 @@ int main() {
                 check_lm(rows, V, d, true, false);
                 check_lm(rows, V, d, false, false);
             }
+    // what the GPU tests of the lean plan and of its kernel's two row blocks take to reach them
+    const LmPlan usual = lm_plan(256, 200001, 192, true), lean = lm_plan(256, 200001, 192, true, true);
+    CHECK(usual.tile && 256 + lm_scratch_bytes(usual, 256, true) > 16u << 20, "usual plan");
+    CHECK(lean.grid && lean.nrb == 2 && 256 + lm_scratch_bytes(lean, 256, true) <= 16u << 20, "lean plan");
+    for (int V : {262209, 262176, 300007}) CHECK(lm_plan(200, V, 64, true).grid && lm_plan(200, V, 64, true).nrb == 2, "V %d", V);
+    CHECK(!lm_plan(200, 262183, 80, true).tile && !lm_plan(200, 262183, 80, true).dma, "register-staged");
     std::printf("%lld shapes, %d failures\n", shapes, fails);
     return fails != 0;
 }

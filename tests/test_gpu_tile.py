@@ -64,10 +64,11 @@ def test_lm_head_tile_few_rows(rows, V, d, k):
 
 
 def test_lm_head_tile_against_the_lean_plan():
-    """The static-scratch call keeps fitting 16 MiB by the plan with fewer slices."""
+    """The static-scratch call keeps fitting 16 MiB by the plan with fewer slices (two row blocks of the streaming
+    kernel, from 196616 tokens on at 256 rows; plan_check.cpp holds that the usual plan does not fit here)."""
     import torch
     from paper_2606_03819_amd import binding
-    rows, V, d, k = 256, 170001, 64, 32
+    rows, V, d, k = 256, 200001, 192, 32
     h, lm = _case(rows, V, d, 7, 2)
     lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
     idx, lp = binding.treeflash_marginal_topk_static(h, lm, k, lse=lse)
@@ -75,3 +76,16 @@ def test_lm_head_tile_against_the_lean_plan():
     lse2 = torch.empty_like(lse)
     idx2, lp2 = binding.treeflash_marginal_topk(h, lm, k, lse=lse2)
     assert torch.equal(idx, idx2) and (lse - lse2).abs().max() <= 1e-4
+
+
+# 129 to 256 rows over vocabularies past the tile kernel's slices (262176 tokens on): the streaming kernel's two row
+# blocks, its register-staged form at widths that are no multiple of 64; short and long lists
+@pytest.mark.parametrize("rows,V,d,k", [(129, 262209, 64, 8), (256, 262176, 192, 70), (193, 300007, 64, 33),
+                                        (200, 262183, 80, 16)])
+def test_lm_head_two_row_blocks(rows, V, d, k):
+    import torch
+    from paper_2606_03819_amd import binding
+    h, lm = _case(rows, V, d, rows + V, 2)
+    lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
+    idx, lp = binding.treeflash_marginal_topk(h, lm, k, lse=lse)
+    _check(h, lm, k, idx, lp, lse)
