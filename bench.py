@@ -65,7 +65,7 @@ def kernel_source_digest() -> str:
 
 def lm_kernel_pattern(rows: int, d: int) -> str:
     """Regex for the bf16 LM-head kernel instance the plan picks for `rows` rows over a
-    vocabulary of more than 65536 tokens: the block-tiled kernel beyond 128 rows, else the
+    vocabulary of more than 65536 tokens, d above 640: the block-tiled kernel beyond 128 rows, else the
     LDS-DMA kernel (widths that are a multiple of its k step, 64), the block-tiled kernel
     above 64 rows and the register-staged one (other widths)."""
     nt = 1 if rows <= 32 else (2 if rows <= 64 else 4)

@@ -1040,6 +1040,9 @@ static hipError_t dispatch_lm_bf16(const LmPlan& p, const uint16_t* x, long ldx,
         if (p.NT == 2)   // 33..64 rows: one activation tile per wave of the grid
             return launch_lm_dma<LONG, TF_LM_DMA_WM, 2, TF_LM_DMA_NW_SINGLE, TF_LM_DMA_KC, true, 1, TF_LM_DMA_SINGLE_WB>(
                 x, ldx, w, sh, p.map, nb, V, sl2, part, diag, st);
+        if (p.NT == 8)   // 256-row blocks
+            return launch_lm_dma<LONG, 2, 8, 8, TF_LM_DMA_KC, false, 1, 2>(x, ldx, w, sh, p.map, nb, V, sl2, part, diag,
+                                                                           st);
         // 65 rows up: one row block or two
         return launch_lm_dma<LONG, TF_LM_DMA_WM, 4, TF_LM_DMA_NW_SINGLE, TF_LM_DMA_KC, true, 1, TF_LM_DMA_SINGLE_WB>(
             x, ldx, w, sh, p.map, nb, V, sl2, part, diag, st);

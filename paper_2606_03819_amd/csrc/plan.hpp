@@ -44,15 +44,15 @@ inline int plan_nt(int rows) { return rows <= 32 ? 1 : (rows <= 64 ? 2 : 4); }
 // workgroup per (tile range, row block), the row blocks of a range on
 // consecutive workgroups so that they share its tiles through L2.  One row
 // block: the tiles spread over TF_LM_WORKGROUPS workgroups; more row blocks:
-// lm_tile_plan below.  fp32 (SIMT kernel): 16 rows and 1 to 8 tiles (256 tokens)
-// per workgroup.
+// lm_tile_plan below, narrow widths apart.  fp32 (SIMT kernel): 16 rows and 1 to
+// 8 tiles (256 tokens) per workgroup.
 struct LmPlan {
     int NT, WM, NW, chunk, nrb, ntiles, nk;
     int WB = 1;   // waves along the activation tiles (a grid of NW / WB x WB waves)
     bool grid = false;   // the DMA kernel's 2 x 2 wave grid (33 to 256 rows)
     SliceMap map;
     bool wnt;   // weight loads carry the non-temporal hint
-    bool dma;   // the LDS-DMA kernel (32-row tiles or the grid)
+    bool dma;   // the LDS-DMA kernel (32-row tiles, the grid, or 256-row blocks)
     // the block-tiled kernel (tile_gemm.hpp): WM and NT count 16-row tiles of
     // one of its 2 x 2 waves
     bool tile = false;
@@ -168,6 +168,22 @@ inline LmPlan lm_tile_plan(int rows, int V, int d) {
     return p;
 }
 
+// Calls of several row blocks' worth of narrow products, which the streaming kernels keep: a k loop of few steps
+// leaves the epilogue to set the time, and the block-tiled kernel's is longer (16-row tiles: more lanes share a row).
+// Whole 256-row blocks at widths of whole k steps; us, streaming / tiled: 400 x 50000 x 128 36 / 42, x 384 49 / 53,
+// x 640 64 / 66, x 33000 x 1024 84 / 79; 1000 x 50000 x 128 67 / 76, x 448 102 / 104, x 512 109 / 108; 1936 x 100000 x
+// 128 198 / 232; 256 rows x 33000 x 64 18.7 / 21.0, x 192 21.7 / 22.9, x 9000 x 192 22.7 / 21.0 (192-row blocks: 300 x
+// 50000 x 64 34.3 / 33.7, x 384 48 / 42).  Other widths, on 128-row blocks, where the tiled kernel's workgroups leave
+// half the CUs of their last round idle (400 x 9000 x 272 34 / 40, x 720 58 / 60, 512 x 33000 x 112 40 / 45), and
+// of two row blocks at the narrowest (400 x 100000 x 112 74 / 81, x 208 96 / 95).
+inline bool lm_narrow(const LmPlan& t, int rows, int d) {
+    if (rows < kTileMinRows) return false;
+    if (d % TF_LM_DMA_KC == 0) return t.NT == 8 && d <= (t.nrb == 1 ? 128 : t.nrb <= 3 ? 640 : 448);
+    if (t.nrb == 1) return false;
+    const long long rounds = cdiv(t.blocks(), kNumCUs);
+    return d < (100ll * t.blocks() <= 55 * rounds * kNumCUs ? 512 : t.nrb == 2 ? 160 : 0);
+}
+
 // `lean`: the plan with the fewest slices (and so partials) for 129-256 rows,
 // for callers whose scratch is short; also taken for vocabularies whose
 // block-tiled slices would be too many for long lists.
@@ -176,7 +192,7 @@ inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
     const bool few = per > 1 && (per <= (rows <= 32 ? 7 : 8) || (rows > 64 && d % TF_LM_DMA_KC != 0));
     if (bf16 && d <= kTileMaxK && (rows >= kTileMinRows || (few && !lean))) {
         const LmPlan t = lm_tile_plan(rows, V, d);
-        if (rows > 256 || (!lean && t.nsplit() <= kMaxSplitsLong)) return t;
+        if (!lm_narrow(t, rows, d) && (rows > 256 || (!lean && t.nsplit() <= kMaxSplitsLong))) return t;
     }
     LmPlan p;
     p.ntiles = cdiv(V, 32);
@@ -184,11 +200,11 @@ inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
     p.dma = false;
     if (bf16) {
         p.NT = plan_nt(rows);
-        // k in whole 64-wide steps: the DMA kernel -- 32-row tiles, or the
-        // 2 x 2 wave grid (two row blocks: the lean plan)
+        // k in whole 64-wide steps: the DMA kernel -- 32-row tiles, the
+        // 2 x 2 wave grid (up to two row blocks), else 256-row blocks
         p.nrb = cdiv(rows, 32 * p.NT);
         p.grid = p.NT >= 2 && p.nrb <= 2 && d % TF_LM_DMA_KC == 0;
-        p.dma = p.grid || (p.NT == 1 && d % TF_LM_DMA_KC == 0);
+        p.dma = d % TF_LM_DMA_KC == 0;
         if (p.dma && p.NT == 1) {
             p.WM = TF_LM_DMA_NT1_WM;
             p.NW = TF_LM_DMA_NT1_NW;
@@ -196,6 +212,13 @@ inline LmPlan lm_plan(int rows, int V, int d, bool bf16, bool lean = false) {
             p.WM = TF_LM_DMA_WM;
             p.NW = TF_LM_DMA_NW_SINGLE;
             p.WB = TF_LM_DMA_SINGLE_WB;
+        } else if (p.dma) {
+            // eight waves in a 4 x 2 grid of 2 weight x 4 activation tiles, one workgroup per CU
+            p.NT = 8;
+            p.nrb = cdiv(rows, 256);
+            p.WM = 2;
+            p.NW = 8;
+            p.WB = 2;
         } else {
             p.WM = lm_wm(p.NT);
             p.NW = lm_nw(p.NT);

@@ -89,3 +89,19 @@ def test_lm_head_two_row_blocks(rows, V, d, k):
     lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
     idx, lp = binding.treeflash_marginal_topk(h, lm, k, lse=lse)
     _check(h, lm, k, idx, lp, lse)
+
+
+# either side of the widths below which many rows stay on the streaming kernels: 256-row blocks (up to 640 columns for
+# two or three of them, 448 for more, 128 for one) and, at widths that are no multiple of 64, 128-row blocks
+@pytest.mark.parametrize("rows,V,d,k", [
+    (400, 3001, 64, 32), (512, 9001, 640, 70), (512, 9001, 704, 70), (1000, 5003, 448, 64), (1000, 5003, 512, 8),
+    (256, 40001, 128, 16), (256, 40001, 192, 100), (300, 4099, 496, 16), (300, 4099, 528, 33), (600, 20003, 144, 64),
+    (513, 8225, 80, 5), (385, 300, 48, 100),
+])
+def test_lm_head_narrow_widths(rows, V, d, k):
+    import torch
+    from paper_2606_03819_amd import binding
+    h, lm = _case(rows, V, d, rows + V, 2 if d < 512 else 1)
+    lse = torch.empty((1, rows), dtype=torch.float32, device="cuda")
+    idx, lp = binding.treeflash_marginal_topk(h, lm, k, lse=lse)
+    _check(h, lm, k, idx, lp, lse)
