@@ -157,112 +157,17 @@ __global__ __launch_bounds__(256) void rmsnorm_rows_bf16_kernel(const uint16_t* 
     }
 }
 
-// ------------------------------------------------------------ plain products
+// ------------------------------------------------------------ fp32
 
-// one activation: a bf16 hi/lo pair interleaved by 8
-__device__ __forceinline__ float load_act(const uint16_t* p, size_t i) {
-    const size_t q = (i >> 3) * 16 + (i & 7);
-    return bf16_bits_to_f32(p[q]) + bf16_bits_to_f32(p[q + 8]);
-}
-__device__ __forceinline__ void store_act(uint16_t* p, size_t i, float v) {
-    const size_t q = (i >> 3) * 16 + (i & 7);
-    const uint32_t hi = f32_to_bf16_bits(v);
-    p[q] = (uint16_t)hi;
-    p[q + 8] = (uint16_t)f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
-}
-
-// The bf16 products whose widths pass the block-tiled kernel's offsets
-// (tile_width_ok): out[r, n] = epi( x_r . W[n] )
-// with x_r = [x0 row of r's drafter state (d0 wide) ; x1 row r (K - d0 wide)].
-// A workgroup holds 16 rows x 16 output columns; the reduction range streams
-// through LDS in 64-wide chunks (every thread copies four activation and four
-// weight values per chunk, consecutive threads consecutive k, the next
-// chunk's loads in flight while this one is multiplied), and each thread
-// accumulates its output with one fmaf chain in k order.
+// The approximator's fp32 products (small models): out[r, n] = epi( x_r . W[n] )
+// with x_r = [x0 row of r's drafter state (d0 wide) ; x1 row r (K - d0 wide)],
+// 16 rows x 16 output columns a workgroup.
 //   GATE:  act = silu(x . W_gate[n]) * (x . W_up[n])  (W_up null: silu alone)
 //   else:  out = h[r's drafter state, n] + x . W[n]   (down projection, linear)
-// ACT: x1 holds activations (load_act).
-template <class T, bool GATE, bool ACT = false>
-__global__ __launch_bounds__(256) void mlp_simt_kernel(const T* __restrict__ wa, const T* __restrict__ wb, int N,
-                                                       long K, const T* __restrict__ x0, int d0,
-                                                       const T* __restrict__ x1, long ld1, RowTable rt, int rows,
-                                                       const T* __restrict__ h, T* __restrict__ out, int ldo) {
-    __shared__ float xs[16][65];
-    __shared__ float ws[2][16][65];
-    const int tid = threadIdx.x;
-    const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16;
-    const int tx = tid & 15, ty = tid >> 4;
-    const bool two = GATE && wb != nullptr;
-    // the x0 row (drafter state) of each of the tile's rows
-    auto state_of = [&](int r) {
-        const int s = r / rt.Rs;
-        return s * rt.gamma + rt.depth(r - s * rt.Rs) - 1;
-    };
-    // this thread's copies of a chunk: rows (and weight rows) e / 64, k e % 64, e = tid + 256 j
-    int xrow[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = r0 + ((tid + 256 * j) >> 6);
-        xrow[j] = r < rows ? state_of(r) : -1;
-    }
-    float px[4], pw[4], pw2[4];
-    auto fetch = [&](long k0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = tid + 256 * j;
-            const int rr = e >> 6;
-            const long k = k0 + (e & 63);
-            const int r = r0 + rr, n = n0 + rr;
-            px[j] = pw[j] = pw2[j] = 0.f;
-            if (xrow[j] >= 0 && k < K) {
-                if constexpr (ACT)
-                    px[j] = load_act(x1, (size_t)r * ld1 + k);
-                else
-                    px[j] = k < d0 ? load_elem(x0, (size_t)xrow[j] * d0 + k) : load_elem(x1, (size_t)r * ld1 + (k - d0));
-            }
-            if (n < N && k < K) {
-                pw[j] = load_elem(wa, (size_t)n * K + k);
-                if (two) pw2[j] = load_elem(wb, (size_t)n * K + k);
-            }
-        }
-    };
-    float acc_a = 0.f, acc_b = 0.f;
-    fetch(0);
-    for (long k0 = 0; k0 < K; k0 += 64) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = tid + 256 * j;
-            xs[e >> 6][e & 63] = px[j];
-            ws[0][e >> 6][e & 63] = pw[j];
-            ws[1][e >> 6][e & 63] = pw2[j];
-        }
-        __syncthreads();
-        if (k0 + 64 < K) fetch(k0 + 64);   // the next chunk's loads run under this chunk's products
-        const int kn = (int)min(64l, K - k0);
-        for (int kk = 0; kk < kn; ++kk) {
-            const float xv = xs[ty][kk];
-            acc_a = fmaf(xv, ws[0][tx][kk], acc_a);
-            if (two) acc_b = fmaf(xv, ws[1][tx][kk], acc_b);
-        }
-        __syncthreads();
-    }
-    const int r = r0 + ty, n = n0 + tx;
-    if (r >= rows || n >= N) return;
-    if constexpr (GATE) {
-        float a = acc_a / (1.0f + expf(-acc_a));
-        if (two) a *= acc_b;
-        store_act(out, (size_t)r * ldo + n, a);   // an activation row: ldo elements (pairs)
-    } else {
-        store_elem(out, (size_t)r * ldo + n, load_elem(h, (size_t)state_of(r) * N + n) + acc_a);
-    }
-}
-
-// The approximator's fp32 products (small models), with the arguments of the
-// plain kernel above.  A handful of workgroups and one fmaf chain an output:
-// what bounds it is the chain and the round trips to memory, so a chunk is 256
-// columns wide (all of x and W for the widths such models have, in one or two
-// trips, the next chunk's in flight while one is multiplied) and LDS is read 16
-// bytes at a time.  31 rows, I = d = 256: gate/up 29.5 -> 10.3 us, down 9.6
+// A handful of workgroups and one fmaf chain an output: what bounds it is the
+// chain and the round trips to memory, so a chunk is 256 columns wide (all of x
+// and W for the widths such models have, in one or two trips, the next chunk's in
+// flight while one is multiplied) and LDS is read 16 bytes at a time.  31 rows, I = d = 256: gate/up 29.5 -> 10.3 us, down 9.6
 // -> 4.9 us against 64-wide chunks and 4-byte reads.
 template <bool GATE>
 __global__ __launch_bounds__(256) void mlp_f32_kernel(const float* __restrict__ wa, const float* __restrict__ wb, int N,
@@ -470,8 +375,9 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
     f.hh = hh;
     f.states = states;
     f.rt = rt;
+    const bool wide = tile_wide(d + (long long)ew);   // the input projections' rows
     hipError_t e;
-    if (mlp_dma_gate_applies(true, b, rt.gamma, rt.Rs, d, I, ew, rt.bigram)) {
+    if (!wide && mlp_dma_gate_applies(true, b, rt.gamma, rt.Rs, d, I, ew, rt.bigram)) {
         const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, ew, I, swiglu);
         launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
                                counters, pg.items, stream);
@@ -479,7 +385,7 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
                                            counters);
         e = swiglu ? launch_mlp_dma<kMlpWGateUp, kMlpEpiSwiGLU>(ag, pg, stream)
                    : launch_mlp_dma<kMlpWPlain, kMlpEpiSiLU>(ag, pg, stream);
-    } else if (rt.bigram) {
+    } else if (rt.bigram && !wide) {
         const RowTable tt = make_token_table(rt.gamma, rt.M);
         const int tokens = b * tt.Rs;
         launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, tt, 1, eps, ht, et, diag,
@@ -503,22 +409,22 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
         f.t2 = t2;
         e = launch_tile_finish(f, stream);
     } else {
-        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
+        launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
                                counters, 0, stream);
-        const TilePlan ph = tile_state_plan(states, N, d);
+        const TilePlan ph = tile_state_plan(states, N, d, wide);
         TileProductArgs a{};
         a.seg[0] = TileSegment{wg, wu, htb, states, hh};
         a.nseg = 1;
         a.gateup = swiglu;
         a.N = N;
-        a.Kw = 2 * d;
+        a.Kw = d + ew;
         a.K = d;
         a.ldx = d;
         e = launch_tile_product(ph, false, a, stream);
         if (e != hipSuccess) return e;
         f.nhh = ph.S;
-        e = tile_product_finished(tile_input_plan(rows, N, d), false, wg + d, swiglu ? wu + d : nullptr, etb, d, 2 * d,
-                                  d, partial, f, stream);
+        e = tile_product_finished(tile_input_plan(rows, N, ew, wide), false, wg + d, swiglu ? wu + d : nullptr, etb, ew,
+                                  d + ew, ew, partial, f, stream);
     }
     if (e != hipSuccess) return e;
     TileFinish r{};
@@ -533,34 +439,6 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
                                  2l * I, I, I, partial, r, stream);
 }
 
-// The plain kernels: fp32, and bf16 widths past the block-tiled kernel's offsets.
-template <class T>
-static hipError_t launch_arapprox_simt(const void* h, const int32_t* root, const int32_t* context,
-                                       const int32_t* topk_idx, const void* emb, const void* gain_h,
-                                       const void* gain_e, const void* w_gate, const void* w_up, const void* w_down,
-                                       int b, int d, int I, int V, const RowTable& rt, int npre, float eps, void* ht,
-                                       void* et, void* act, void* hp, int* diag, hipStream_t stream) {
-    const int rows = b * rt.Rs, ew = npre * d;
-    launch_norms<T>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag, nullptr, 0,
-                    stream);
-    const dim3 gg(cdiv(I, 16), cdiv(rows, 16)), gd(cdiv(d, 16), cdiv(rows, 16));
-    const T *wg = static_cast<const T*>(w_gate), *wu = static_cast<const T*>(w_up), *wd = static_cast<const T*>(w_down);
-    const T *xh = static_cast<const T*>(ht), *xe = static_cast<const T*>(et), *hb = static_cast<const T*>(h);
-    T *ab = static_cast<T*>(act), *ob = static_cast<T*>(hp);
-    if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL(mlp_f32_kernel<true>, gg, dim3(256), 0, stream, wg, wu, I, d + ew, xh, d, xe, ew, rt, rows,
-                           nullptr, ab, I);
-        hipLaunchKernelGGL(mlp_f32_kernel<false>, gd, dim3(256), 0, stream, wd, nullptr, d, I, nullptr, 0, ab, I, rt,
-                           rows, hb, ob, d);
-    } else {
-        hipLaunchKernelGGL((mlp_simt_kernel<T, true>), gg, dim3(256), 0, stream, wg, wu, I, (long)d + ew, xh, d, xe,
-                           (long)ew, rt, rows, nullptr, ab, I);
-        hipLaunchKernelGGL((mlp_simt_kernel<T, false, true>), gd, dim3(256), 0, stream, wd, nullptr, d, (long)I,
-                           nullptr, 0, ab, (long)I, rt, rows, hb, ob, d);
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_arapprox(const void* h, const int32_t* root, const int32_t* context, const int32_t* topk_idx,
                            const void* emb, const void* gain_h, const void* gain_e, const void* w_gate,
                            const void* w_up, const void* w_down, int b, int gamma, int d, int I, int V, int k,
@@ -570,15 +448,20 @@ hipError_t launch_arapprox(const void* h, const int32_t* root, const int32_t* co
     const int npre = bigram ? 2 : 1;
     const int ew = npre * d;
     const int rows = b * rt.Rs;
-    if (bf16) {
-        if (tile_width_ok(d, ew, I))
-            return launch_arapprox_tile(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d,
-                                        I, V, rt, eps, ht, et, act, hp, mlp_partial, counters, hh, diag, stream);
-        return launch_arapprox_simt<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down,
-                                              b, d, I, V, rt, npre, eps, ht, et, act, hp, diag, stream);
-    }
-    return launch_arapprox_simt<float>(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d, I,
-                                       V, rt, npre, eps, ht, et, act, hp, diag, stream);
+    if (bf16)
+        return launch_arapprox_tile(h, root, context, topk_idx, emb, gain_h, gain_e, w_gate, w_up, w_down, b, d, I, V, rt,
+                                    eps, ht, et, act, hp, mlp_partial, counters, hh, diag, stream);
+    launch_norms<float>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag, counters, 0,
+                        stream);
+    const float *xh = static_cast<const float*>(ht), *xe = static_cast<const float*>(et);
+    float* ab = static_cast<float*>(act);
+    hipLaunchKernelGGL(mlp_f32_kernel<true>, dim3(cdiv(I, 16), cdiv(rows, 16)), dim3(256), 0, stream,
+                       static_cast<const float*>(w_gate), static_cast<const float*>(w_up), I, d + ew, xh, d, xe, ew, rt,
+                       rows, nullptr, ab, I);
+    hipLaunchKernelGGL(mlp_f32_kernel<false>, dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
+                       static_cast<const float*>(w_down), nullptr, d, I, nullptr, 0, ab, I, rt, rows,
+                       static_cast<const float*>(h), static_cast<float*>(hp), d);
+    return hipGetLastError();
 }
 
 hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int32_t* topk_idx, const void* emb,
@@ -599,8 +482,8 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
                                            counters);
         return launch_mlp_dma<kMlpWPlain, kMlpEpiResidual>(al, pl, stream);
     }
-    const bool tile = bf16 && tile_width_ok(d, d, d);
-    if (tile) {
+    if (bf16) {
+        const bool wide = tile_wide(2ll * d);
         // the h~ half once per drafter state, then the e~ half with the residual
         const int states = b * gamma;
         launch_norms<uint16_t>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
@@ -613,7 +496,7 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
         ah.Kw = 2 * d;
         ah.K = d;
         ah.ldx = d;
-        const TilePlan ph = tile_state_plan(states, d, d), pe = tile_input_plan(rows, d, d);
+        const TilePlan ph = tile_state_plan(states, d, d, wide), pe = tile_input_plan(rows, d, d, wide);
         const hipError_t e = launch_tile_product(ph, false, ah, stream);
         if (e != hipSuccess) return e;
         TileFinish f{};
@@ -629,21 +512,12 @@ hipError_t launch_arapprox_linear(const void* h, const int32_t* root, const int3
         return tile_product_finished(pe, false, wl + d, nullptr, static_cast<const uint16_t*>(et), d, 2 * d, d,
                                      mlp_partial, f, stream);
     }
-    const dim3 grid(cdiv(d, 16), cdiv(rows, 16));
-    if (bf16) {
-        launch_norms<uint16_t>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
-                               counters, 0, stream);
-        hipLaunchKernelGGL((mlp_simt_kernel<uint16_t, false>), grid, dim3(256), 0, stream,
-                           static_cast<const uint16_t*>(w_lin), nullptr, d, 2l * d, static_cast<const uint16_t*>(ht), d,
-                           static_cast<const uint16_t*>(et), (long)d, rt, rows, static_cast<const uint16_t*>(h),
-                           static_cast<uint16_t*>(hp), d);
-    } else {
-        launch_norms<float>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag,
-                            counters, 0, stream);
-        hipLaunchKernelGGL(mlp_f32_kernel<false>, grid, dim3(256), 0, stream, static_cast<const float*>(w_lin), nullptr,
-                           d, 2 * d, static_cast<const float*>(ht), d, static_cast<const float*>(et), d, rt, rows,
-                           static_cast<const float*>(h), static_cast<float*>(hp), d);
-    }
+    launch_norms<float>(h, root, nullptr, topk_idx, emb, gain_h, gain_e, b, d, V, rt, 1, eps, ht, et, diag, counters, 0,
+                        stream);
+    hipLaunchKernelGGL(mlp_f32_kernel<false>, dim3(cdiv(d, 16), cdiv(rows, 16)), dim3(256), 0, stream,
+                       static_cast<const float*>(w_lin), nullptr, d, 2 * d, static_cast<const float*>(ht), d,
+                       static_cast<const float*>(et), d, rt, rows, static_cast<const float*>(h), static_cast<float*>(hp),
+                       d);
     return hipGetLastError();
 }
 

@@ -255,6 +255,7 @@ struct TilePlan {
     int nrb, ntw;      // row blocks, weight tiles
     int S, per, nk;    // splits, steps of a split, steps in all
     double us;         // the model's time
+    bool wide;         // rows past a descriptor's offsets
     int items() const { return nrb * ntw * S; }
 };
 
@@ -263,15 +264,20 @@ struct TilePlan {
     F(8, 8, false) F(6, 8, false) F(5, 8, false) F(4, 8, false) F(4, 4, false) F(2, 4, false) F(4, 2, false) \
     F(8, 4, true) F(4, 4, true) F(2, 4, true) F(4, 2, true)
 
+// The one shape of rows past a descriptor's offsets.
+constexpr int kTileWideW = 4, kTileWideX = 2;
+
 constexpr int kTileSplits = 8;             // most splits
+constexpr int kTileWideSplits = 64;        // ... of such rows: few tiles, and a long reduction
 constexpr int kTileSplitFloats = 16384;    // most fp32 partial sums of a row, over its splits
 constexpr int kTileSplitRows = 2048;       // rows up to which products are split (more rows make tiles enough)
 constexpr int kTileMinSteps = 4;           // fewest steps of a split
 
 // Partial sums a row's split products may take (floats); none once two splits pass the limit.
-inline long long tile_split_floats(int rows, long long N) {
+inline long long tile_split_floats(int rows, long long N, bool wide = false) {
     if (rows > kTileSplitRows || 2 * N > kTileSplitFloats) return 0;
-    return N * kTileSplits < kTileSplitFloats ? N * kTileSplits : kTileSplitFloats;
+    const long long most = N * (wide ? kTileWideSplits : kTileSplits);
+    return most < kTileSplitFloats ? most : kTileSplitFloats;
 }
 
 // The shape and split that a simple time model finds fastest.  A step takes
@@ -285,14 +291,17 @@ inline long long tile_split_floats(int rows, long long N) {
 // 160 x 256 130 / 130; 455 x 19456 x 2560 160 x 256 55 / 55, 192 x 256 59 / 59, 256 x 256 72 / 67;
 // 256 x 8192 x 4096 128 x 128 in two splits 30 / 30, 64 x 128 33 / 41; pairs:
 // 905 x 4096 x 4096 128 x 128 56 / 51, 256 x 128 in two splits 60 / 62.
-inline TilePlan tile_plan(int rows, int N, int K, int nseg, bool paired, int max_splits, bool tables) {
+inline TilePlan tile_plan(int rows, int N, int K, int nseg, bool paired, int max_splits, bool tables,
+                          bool wide = false) {
     TilePlan best{};
     best.us = 1e30;
     const int np = paired ? 2 : 1;
     const int nk = cdiv(K, 64);
     const double wbytes = 2.0 * N * K * nseg;
     auto consider = [&](int WMT, int NXT) {
+        if (wide && (WMT != kTileWideW || NXT != kTileWideX)) return;
         TilePlan p;
+        p.wide = wide;
         p.WMT = WMT;
         p.NXT = NXT;
         p.nk = nk;
@@ -301,7 +310,7 @@ inline TilePlan tile_plan(int rows, int N, int K, int nseg, bool paired, int max
         const double copy = 32.0 * (WMT + NXT * np) * 128 / (paired ? 64e3 : (p.nrb >= 4 ? 55e3 : 40e3));
         const double mfma = 32.0 * WMT * NXT * np * 1.5 / 2100;
         const double step = copy > mfma ? copy : mfma;
-        for (int S = 1; S <= max_splits; S += S < 4 ? 1 : 2) {
+        for (int S = 1; S <= max_splits; S += S < 4 ? 1 : S < 16 ? 2 : 8) {
             if (S > 1 && (nk < S * kTileMinSteps || (long long)S * N > tile_split_floats(rows, N))) break;
             p.per = cdiv(nk, S);
             p.S = cdiv(nk, p.per);
@@ -322,18 +331,25 @@ inline TilePlan tile_plan(int rows, int N, int K, int nseg, bool paired, int max
     return best;
 }
 
-// Widest reduction or activation row whose byte offsets within a tile stay
-// below kTileSpan; wider ones (weights of more than 2^20 columns, and so of
-// few rows) take a plain kernel.
-inline bool tile_width_ok(int d, int ew, int I) { return d <= kTileMaxK - ew && I <= kTileMaxK; }
+// Widest weight row whose byte offsets within a tile (and its activations')
+// stay below kTileSpan; a product of wider ones, of more than 2^20 columns and so
+// of few weight rows, takes the wide kernels: one tile shape, up to 64 splits.
+// The weight-streaming kernel before them / now, us: 130 rows, d = 16, I = 2^20 +
+// 16 1048 / 1916, 17 rows, d = 2^19 + 64, I = 64 1034 / 1262.
+inline bool tile_wide(long long width) { return width > kTileMaxK; }
 
 // The h~ half of an input projection ([states, d] into fp32 tables of N
 // columns, the readers add its splits), the e~ half, the down projection.
-inline TilePlan tile_state_plan(int states, int N, int d) { return tile_plan(states, N, d, 1, false, 2, true); }
-inline TilePlan tile_input_plan(int rows, int N, int ew) {
-    return tile_plan(rows, N, ew, 1, false, kTileSplits, false);
+inline TilePlan tile_state_plan(int states, int N, int d, bool wide) {
+    return tile_plan(states, N, d, 1, false, wide ? kTileWideSplits : 2, true, wide);
 }
-inline TilePlan tile_down_plan(int rows, int d, int I) { return tile_plan(rows, d, I, 1, true, kTileSplits, false); }
+inline TilePlan tile_input_plan(int rows, int N, int ew, bool wide) {
+    return tile_plan(rows, N, ew, 1, false, wide ? kTileWideSplits : kTileSplits, false, wide);
+}
+inline TilePlan tile_down_plan(int rows, int d, int I) {
+    const bool wide = tile_wide(I);
+    return tile_plan(rows, d, I, 1, true, wide ? kTileWideSplits : kTileSplits, false, wide);
+}
 // the bigram rows' products, once per state and previous token
 inline TilePlan tile_token_plan(int tokens, int N, int d) { return tile_plan(tokens, N, d, 3, false, 1, true); }
 
@@ -477,20 +493,20 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
     const size_t es = bf16 ? 2 : 4;
     const int rows1 = b * gamma, rows2 = b * R;   // R >= gamma
     const size_t tokens = (size_t)b * bigram_tokens(gamma, k);
-    const bool tables = bf16 && bigram && tile_width_ok(d, npre * d, I);
+    const bool tables = bf16 && bigram && !tile_wide(d + (long long)npre * d);
     size_t mp = 0, hhf = 0, erows = (size_t)rows2 * npre;
     Workspace w;
     w.ncounters = 0;
     if (bf16) {
         // split products: at most kTileSplitFloats a row, of at most kTileSplitRows rows
-        const int rs = rows2 < kTileSplitRows ? rows2 : kTileSplitRows;
+        const int rs = rows2 < kTileSplitRows ? rows2 : kTileSplitRows, ss = rows1 < rs ? rows1 : rs;
+        const bool wide = tile_wide(d + (long long)npre * d) || tile_wide(I);
         for (const long long N : {2ll * I, (long long)I, (long long)d}) {
-            const size_t f = (size_t)rs * tile_split_floats(rs, N);
-            mp = mp > f ? mp : f;
-            // the h~ tables: two splits of up to kTileSplitRows states, one of more
-            const long long two = tile_split_floats(1, N) > 0 ? 2ll * (rows1 < kTileSplitRows ? rows1 : kTileSplitRows) : 0;
-            const size_t hf = (size_t)N * (rows1 > two ? rows1 : two);
-            hhf = hhf > hf ? hhf : hf;
+            const long long f = tile_split_floats(1, N, wide);
+            mp = mp > (size_t)(rs * f) ? mp : (size_t)(rs * f);
+            // the h~ tables: two splits (wide: as above) of up to kTileSplitRows states, one of more
+            const long long s2 = ss * (wide || f == 0 ? f : 2 * N), s1 = rows1 * N;
+            hhf = hhf > (size_t)(s1 > s2 ? s1 : s2) ? hhf : (size_t)(s1 > s2 ? s1 : s2);
         }
         if (tables) {
             const size_t ld = 2 * (size_t)I > (size_t)d ? 2 * (size_t)I : (size_t)d;
@@ -506,7 +522,7 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
                 w.ncounters = w.ncounters > q.items ? w.ncounters : q.items;
             };
             if (mlp_dma_linear_rows(n, d)) need(mlp_dma_linear_plan(n, d));
-            if (tile_width_ok(d, npre * d, I) && mlp_dma_gate_rows(n, d, I, npre * d, bigram)) {
+            if (!tile_wide(d + (long long)npre * d) && mlp_dma_gate_rows(n, d, I, npre * d, bigram)) {
                 need(mlp_dma_gate_plan(n, d, npre * d, I, true));
                 need(mlp_dma_gate_plan(n, d, npre * d, I, false));
             }

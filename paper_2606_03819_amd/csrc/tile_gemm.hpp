@@ -38,6 +38,10 @@
 //
 // PAIRED: the activation rows hold bf16 hi/lo pairs interleaved by 8 (256
 // bytes a step), both multiplied by the same weight fragment.
+//
+// WIDE: rows too long for a descriptor's offsets (more than 2^20 elements).
+// Copies go through 64-bit addresses, and what lies past an operand's end comes
+// from a piece of zeros.
 #pragma once
 
 #include <utility>
@@ -76,7 +80,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t byte_buffer(const void* p, siz
                                              0x00020000);
 }
 
-template <int WMT, int NXT, bool PAIRED = false, bool DEEP = false>
+template <int WMT, int NXT, bool PAIRED = false, bool DEEP = false, bool WIDE = false>
 struct TileGemm {
     static constexpr int NTH = 256;
     static constexpr int WROWS = 32 * WMT;              // weight rows of a workgroup
@@ -106,6 +110,9 @@ struct TileGemm {
     int lane, wave, wa, wb;
     __amdgpu_buffer_rsrc_t rw[2], rx;   // weight copy i reads through rw[i & 1]
     unsigned wof[WI], xof[XI];          // byte offsets of this lane's pieces
+    const uint16_t *wp[WI], *xp[XI];    // WIDE: their addresses at step 0, `zeros` apart from the live ones
+    const uint16_t* zeros;
+    unsigned wlive, xlive;
     int krem;                           // columns of the last step, 64 where it is whole
     int step0, last;                    // first and last 64-wide step
 
@@ -136,20 +143,33 @@ struct TileGemm {
             wof[i] = offset(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
         }
     }
+    // WIDE: row r of the tile at row(r), null past the operand's end; `z` is a piece of zeros.
+    template <class RowAddress>
+    __device__ __forceinline__ void weights(const uint16_t* z, const RowAddress& address) {
+        zeros = z;
+        wlive = 0;
+#pragma unroll
+        for (int i = 0; i < WI; ++i) {
+            const int row = wcopy_row(i);
+            const uint16_t* p = address(row);
+            wp[i] = p != nullptr ? p + (((lane & 7) ^ ((row >> 1) & 7)) << 3) : z;
+            wlive |= p != nullptr ? 1u << i : 0u;
+        }
+    }
     // Activations: rows [0, rows) of x, `ld` elements apart; the reduction
     // covers K weight columns.  Steps [s0, s1) of 64 columns.
     __device__ __forceinline__ void activations(const uint16_t* x, long ld, int rows, int K, int s0, int s1) {
-        rx = byte_buffer(x, ((size_t)(rows - 1) * ld + (size_t)K * NP) * 2);
-        krem = s1 * 64 >= K ? K - (K - 1) / 64 * 64 : 64;
+        krem = s1 > (K - 1) / 64 ? K - (K - 1) / 64 * 64 : 64;
+        if constexpr (!WIDE) rx = byte_buffer(x, ((size_t)(rows - 1) * ld + (size_t)K * NP) * 2);
+        xlive = 0;
 #pragma unroll
         for (int i = 0; i < XI; ++i) {
-            if constexpr (PAIRED) {
-                const int row = (wave * XI + i) * 4 + (lane >> 4);
-                const int ls = (lane & 15) ^ (row & 15);
-                xof[i] = row < rows ? (unsigned)((size_t)row * ld * 2) + ls * 16 : (unsigned)kTileSpan;
+            const int row = PAIRED ? (wave * XI + i) * 4 + (lane >> 4) : (wave * XI + i) * 8 + (lane >> 3);
+            const int ls = PAIRED ? (lane & 15) ^ (row & 15) : (lane & 7) ^ ((row >> 1) & 7);
+            if constexpr (WIDE) {
+                xp[i] = x + (size_t)(row < rows ? row : 0) * ld + ls * 8;
+                xlive |= row < rows ? 1u << i : 0u;
             } else {
-                const int row = (wave * XI + i) * 8 + (lane >> 3);
-                const int ls = (lane & 7) ^ ((row >> 1) & 7);
                 xof[i] = row < rows ? (unsigned)((size_t)row * ld * 2) + ls * 16 : (unsigned)kTileSpan;
             }
         }
@@ -159,10 +179,18 @@ struct TileGemm {
 
     template <int CPOL>
     __device__ __forceinline__ void copy_w(int step, int slot, int i) const {
-        buffer_dma16(rw[i & 1], wof[i], step * 128, lds + slot * WST + (wave * WI + i) * 1024, CPOL);
+        unsigned char* const to = lds + slot * WST + (wave * WI + i) * 1024;
+        if constexpr (WIDE)
+            dma16((wlive >> i & 1) != 0 ? wp[i] + (size_t)step * 64 : zeros, to, CPOL);
+        else
+            buffer_dma16(rw[i & 1], wof[i], step * 128, to, CPOL);
     }
     __device__ __forceinline__ void copy_x(int step, int slot, int i) const {
-        buffer_dma16(rx, xof[i], step * XROWB, lds + XOFF + slot * XST + (wave * XI + i) * 1024, 0);
+        unsigned char* const to = lds + XOFF + slot * XST + (wave * XI + i) * 1024;
+        if constexpr (WIDE)
+            dma16((xlive >> i & 1) != 0 ? xp[i] + (size_t)step * (XROWB / 2) : zeros, to, 0);
+        else
+            buffer_dma16(rx, xof[i], step * XROWB, to, 0);
     }
     // Before the copies of the last step: pieces past K go out of range, the
     // weights' too (what lies there times a zero need not be a zero).
@@ -170,7 +198,12 @@ struct TileGemm {
         if (step != last || krem == 64) return;
 #pragma unroll
         for (int i = 0; i < WI; ++i)
-            if ((((lane & 7) ^ ((wcopy_row(i) >> 1) & 7)) << 3) >= krem) wof[i] |= kTailBit;
+            if ((((lane & 7) ^ ((wcopy_row(i) >> 1) & 7)) << 3) >= krem) {
+                if constexpr (WIDE)
+                    wlive &= ~(1u << i);
+                else
+                    wof[i] |= kTailBit;
+            }
     }
     __device__ __forceinline__ void enter_x(int step) {
         if (step != last || krem == 64) return;
@@ -178,11 +211,16 @@ struct TileGemm {
         for (int i = 0; i < XI; ++i) {
             const int ls = PAIRED ? ((lane & 15) ^ (((wave * XI + i) * 4 + (lane >> 4)) & 15)) >> 1
                                   : (lane & 7) ^ ((((wave * XI + i) * 8 + (lane >> 3)) >> 1) & 7);
-            if (ls * 8 >= krem) xof[i] |= kTailBit;
+            if (ls * 8 >= krem) {
+                if constexpr (WIDE)
+                    xlive &= ~(1u << i);
+                else
+                    xof[i] |= kTailBit;
+            }
         }
     }
-    __device__ __forceinline__ void leave() {
-        if (krem == 64) return;
+    __device__ __forceinline__ void leave() {   // (WIDE: one loop an operand)
+        if (WIDE || krem == 64) return;
 #pragma unroll
         for (int i = 0; i < WI; ++i) wof[i] &= ~kTailBit;
 #pragma unroll

@@ -45,6 +45,8 @@ __device__ __forceinline__ void store_residual(const TileFinish& f, int row, int
     *reinterpret_cast<uint2*>(f.out + (size_t)row * f.width + n) = uint2{o01, o23};
 }
 
+__device__ const __align__(16) uint16_t zero_piece[8] = {};   // what wide operands read past their ends
+
 struct TileGrid {
     int nrb, ntw, S, per, nk;   // row blocks, weight tiles, splits of `per` steps, steps in all
 };
@@ -52,10 +54,10 @@ struct TileGrid {
 // Workgroup (row block, weight tile, split, segment), the row blocks of a
 // weight tile on consecutive workgroups of one XCD: they share its weights in
 // that XCD's L2, and the tiles of one split share the activations.
-template <int WMT, int NXT, bool PAIRED>
+template <int WMT, int NXT, bool PAIRED, bool WIDE>
 __global__ __launch_bounds__(256, (TileGemm<WMT, NXT, PAIRED, true>::SMEM <= 80 * 1024 ? 2 : 1)) void tile_product_kernel(
     TileProductArgs a, TileGrid t) {
-    using G = TileGemm<WMT, NXT, PAIRED, true>;
+    using G = TileGemm<WMT, NXT, PAIRED, true, WIDE>;
     extern __shared__ __align__(16) unsigned char dyn[];
     const int nb = gridDim.x, xcd = blockIdx.x & 7;
     int id = xcd * (nb >> 3) + min(xcd, nb & 7) + ((int)blockIdx.x >> 3);
@@ -72,7 +74,13 @@ __global__ __launch_bounds__(256, (TileGemm<WMT, NXT, PAIRED, true>::SMEM <= 80 
     g.init(dyn);
     g.activations(seg.x + (size_t)row0 * a.ldx, a.ldx, rows, a.K, split * t.per, min(t.nk, (split + 1) * t.per));
     const int n = min(a.N - v0, G::WROWS);   // product columns of this tile
-    if (a.gateup) {
+    if constexpr (WIDE) {
+        g.weights(zero_piece, [&](int r) -> const uint16_t* {
+            if (!a.gateup) return r < n ? seg.wa + (size_t)(v0 + r) * a.Kw : nullptr;
+            const int o = (r >> 4) * 8 + (r & 7);
+            return o < n >> 1 ? ((r & 8) != 0 ? seg.wb : seg.wa) + (size_t)((v0 >> 1) + o) * a.Kw : nullptr;
+        });
+    } else if (a.gateup) {
         const int no = n >> 1, o0 = v0 >> 1;
         const size_t bytes = ((size_t)(no - 1) * a.Kw + a.K) * 2;
         g.weights(byte_buffer(seg.wa + (size_t)o0 * a.Kw, bytes), byte_buffer(seg.wb + (size_t)o0 * a.Kw, bytes),
@@ -192,10 +200,10 @@ __global__ __launch_bounds__(256) void tile_finish_kernel(TileFinish f) {
     }
 }
 
-template <int WMT, int NXT, bool PAIRED>
+template <int WMT, int NXT, bool PAIRED, bool WIDE = false>
 static hipError_t launch_shape(const TilePlan& p, const TileProductArgs& a, hipStream_t st) {
-    using G = TileGemm<WMT, NXT, PAIRED, true>;
-    auto kern = tile_product_kernel<WMT, NXT, PAIRED>;
+    using G = TileGemm<WMT, NXT, PAIRED, true, WIDE>;
+    auto kern = tile_product_kernel<WMT, NXT, PAIRED, WIDE>;
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, G::SMEM);
     if (e != hipSuccess) return e;
@@ -205,6 +213,9 @@ static hipError_t launch_shape(const TilePlan& p, const TileProductArgs& a, hipS
 }
 
 hipError_t launch_tile_product(const TilePlan& p, bool paired, const TileProductArgs& a, hipStream_t st) {
+    if (p.wide)
+        return paired ? launch_shape<kTileWideW, kTileWideX, true, true>(p, a, st)
+                      : launch_shape<kTileWideW, kTileWideX, false, true>(p, a, st);
 #define TF_TILE_SHAPE(W, X, P) \
     if (p.WMT == W && p.NXT == X && paired == P) return launch_shape<W, X, P>(p, a, st);
     TF_TILE_SHAPES(TF_TILE_SHAPE)

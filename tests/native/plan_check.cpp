@@ -34,7 +34,8 @@ static void check_product(const TilePlan& p, bool paired, const char* what, cons
 #define KNOWN(W, X, P) known = known || (p.WMT == W && p.NXT == X && paired == P);
     TF_TILE_SHAPES(KNOWN)
 #undef KNOWN
-    CHECK(known, "%s %d x %d", what, p.WMT, p.NXT);
+    CHECK(p.wide || p.WMT * 64ll * (paired ? s.I : s.d) < (long long)kTileSpan, "%s: offsets", what);
+    CHECK(known && (!p.wide || (p.WMT == kTileWideW && p.NXT == kTileWideX)), "%s %d x %d", what, p.WMT, p.NXT);
     CHECK(p.S >= 1 && (p.S - 1) * p.per < p.nk && p.S * p.per >= p.nk, "%s S %d per %d nk %d (b %d d %d I %d)", what, p.S,
           p.per, p.nk, s.b, s.d, s.I);
 }
@@ -76,7 +77,7 @@ static void check_fits(const Shape& s) {
               w.counters - w.hp >= (size_t)rows * s.d * es,
           "rows");
     if (!s.bf16) return;
-    const bool gate = mlp_dma_gate_applies(true, s.b, s.gamma, R, s.d, s.I, ew, s.bigram), wide = !tile_width_ok(s.d, ew, s.I);
+    const bool gate = mlp_dma_gate_applies(true, s.b, s.gamma, R, s.d, s.I, ew, s.bigram), wide = tile_wide(s.d + (long long)ew);
     const size_t erows = s.bigram && !gate && !wide ? (size_t)s.b * bigram_tokens(s.gamma, s.k) : (size_t)rows * npre;
     CHECK(w.act - w.et >= erows * s.d * es, "embeddings (b %d gamma %d k %d)", s.b, s.gamma, s.k);
     auto tables = [&](const TilePlan& p, bool paired, int n, long long N, size_t room, const char* what) {
@@ -87,32 +88,31 @@ static void check_fits(const Shape& s) {
         CHECK(q.part_floats() * 4 <= part && q.items <= w.ncounters && w.hh - w.counters >= (size_t)q.items * 4,
               "pieces (rows %d d %d I %d)", rows, s.d, s.I);
     };
-    if (!wide) {
-        for (int N : {2 * s.I, s.I}) {
-            if (gate) {
-                pieces(mlp_dma_gate_plan(rows, s.d, ew, s.I, N == 2 * s.I));
-            } else if (s.bigram) {
-                if (N == s.I) continue;
-                const int tokens = s.b * bigram_tokens(s.gamma, s.k);
-                check_product(tile_token_plan(tokens, N, s.d), false, "token", s);
-                CHECK(((size_t)states + 2 * (size_t)tokens) * N * 4 <= hh, "token tables");
-            } else {
-                const TilePlan ph = tile_state_plan(states, N, s.d);
-                check_product(ph, false, "state", s);
-                CHECK((size_t)ph.S * states * N * 4 <= hh, "state tables (states %d N %d S %d)", states, N, ph.S);
-                tables(tile_input_plan(rows, N, s.d), false, rows, N, part, "input");
-            }
+    for (int N : {2 * s.I, s.I}) {
+        if (gate && !wide) {
+            pieces(mlp_dma_gate_plan(rows, s.d, ew, s.I, N == 2 * s.I));
+        } else if (s.bigram && !wide) {
+            if (N == s.I) continue;
+            const int tokens = s.b * bigram_tokens(s.gamma, s.k);
+            check_product(tile_token_plan(tokens, N, s.d), false, "token", s);
+            CHECK(((size_t)states + 2 * (size_t)tokens) * N * 4 <= hh, "token tables");
+        } else {
+            const TilePlan ph = tile_state_plan(states, N, s.d, wide);
+            check_product(ph, false, "state", s);
+            CHECK((size_t)ph.S * states * N * 4 <= hh, "state tables (states %d N %d S %d)", states, N, ph.S);
+            tables(tile_input_plan(rows, N, ew, wide), false, rows, N, part, "input");
         }
-        tables(tile_down_plan(rows, s.d, s.I), true, rows, s.d, part, "down");
     }
+    tables(tile_down_plan(rows, s.d, s.I), true, rows, s.d, part, "down");
     if (s.bigram) return;
     if (mlp_dma_linear_applies(true, s.b, s.gamma, R, s.d)) {
         pieces(mlp_dma_linear_plan(rows, s.d));
-    } else if (tile_width_ok(s.d, s.d, s.d)) {
-        const TilePlan ph = tile_state_plan(states, s.d, s.d);
+    } else {
+        const bool lw = tile_wide(2ll * s.d);
+        const TilePlan ph = tile_state_plan(states, s.d, s.d, lw);
         check_product(ph, false, "linear state", s);
         CHECK((size_t)ph.S * states * s.d * 4 <= hh, "linear state tables");
-        tables(tile_input_plan(rows, s.d, s.d), false, rows, s.d, part, "linear input");
+        tables(tile_input_plan(rows, s.d, s.d, lw), false, rows, s.d, part, "linear input");
     }
 }
 
@@ -134,8 +134,8 @@ int main() {
         s.gamma = 1 + rng() % 24;
         s.k = log_uniform(1, 64);
         const int unit = rng() % 3 ? 64 : 16;
-        s.d = std::max(unit, log_uniform(16, 1 << (n % 50 == 0 ? 20 : 14)) / unit * unit);
-        s.I = std::max(unit, log_uniform(16, 1 << (n % 50 == 1 ? 21 : 15)) / unit * unit);
+        s.d = std::max(unit, log_uniform(16, 1 << (n % 50 == 0 ? 21 : 14)) / unit * unit);
+        s.I = std::max(unit, log_uniform(16, 1 << (n % 50 == 1 ? 22 : 15)) / unit * unit);
         s.V = std::max(s.k, log_uniform(64, 400000));
         if ((long long)s.b * cond_rows(s.gamma, s.k, s.bigram) > 1 << 20) continue;
         ++shapes;

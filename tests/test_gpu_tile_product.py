@@ -142,6 +142,13 @@ def test_a_row_past_the_reduction_does_not_leak():
     _check("linear", w, keep)
 
 
-def test_widths_past_the_tile_offsets():
-    """I above 2^20: the plain kernel."""
-    _check("swiglu", _inputs("swiglu", 2, 9, 8, 16, (1 << 20) + 16, 9))
+# weight rows of more than 2^20 columns, in the down projection or the input projections: whole and ragged last steps,
+# one and many splits, more rows than one tile
+@pytest.mark.parametrize("form,b,gamma,k,d,I", [
+    ("swiglu", 2, 9, 8, 16, (1 << 20) + 16), ("silu", 1, 5, 4, 64, (1 << 20) + 64),
+    ("swiglu", 1, 5, 4, (1 << 19) + 64, 64), ("swiglu", 1, 9, 9, (1 << 19) + 48, 48), ("silu", 2, 3, 2, (1 << 19) + 16, 16),
+    ("2prev", 1, 4, 3, 349552, 32), ("2prev", 1, 3, 2, 16, (1 << 20) + 32),
+])
+def test_widths_past_the_tile_offsets(form, b, gamma, k, d, I):
+    print(f"[wide] {form} b{b} gamma{gamma} k{k} d{d} I{I}", flush=True)
+    _check(form, _inputs(form, b, gamma, k, d, I, b * gamma + 9, V=64))
