@@ -377,7 +377,7 @@ static hipError_t launch_arapprox_tile(const void* h, const int32_t* root, const
     f.rt = rt;
     const bool wide = tile_wide(d + (long long)ew);   // the input projections' rows
     hipError_t e;
-    if (!wide && mlp_dma_gate_applies(true, b, rt.gamma, rt.Rs, d, I, ew, rt.bigram)) {
+    if (mlp_dma_gate_applies(b, rt.gamma, rt.Rs, d, I, ew, swiglu, rt.bigram)) {
         const MlpDmaPlan pg = mlp_dma_gate_plan(rows, d, ew, I, swiglu);
         launch_norms<uint16_t>(h, root, context, topk_idx, emb, gain_h, gain_e, b, d, V, rt, npre, eps, ht, et, diag,
                                counters, pg.items, stream);

@@ -419,18 +419,23 @@ inline MlpDmaPlan mlp_dma_linear_plan(int rows, int d) {
 }
 // The input projections of at most 256 rows (bigram rows: 128, beyond that
 // their products are taken per token) on the one-row-block kernel; from 129 rows
-// on only weight matrices of 30 M elements and more, whose stream outweighs what
-// the tiles gain: 241 rows, 4096 x 8192 81 us here / 90 tiled, but 242 rows,
-// 2560 x 5120 61 / 54; 181 rows, the gate alone, 6144 x 4096 66 / 56; at 121 rows
-// 4096 x 8192 59 / 75, 2560 x 5120 46 / 48, 29 rows 2048 x 2048 31 / 30.
-inline bool mlp_dma_gate_rows(long long rows, int d, int I, int ew, int bigram) {
+// on only weight matrices of 30 M elements and more (SwiGLU's two; 40 M the plain
+// gate's one), whose stream outweighs what the tiles gain.  The call from cold
+// weights, us, here / tiled, at 241 and 136 rows, I x d: SwiGLU 3840 x 2560 71 / 65
+// and 64 / 58, 3648 x 4096 83 / 85 and 79 / 77, 4096 x 4096 82 / 87 and 77 / 76,
+// 6144 x 4096 103 / 117 and 98 / 101, 12288 x 4096 164 / 169 and 157 / 166; SiLU
+// 3648 x 4096 77 / 70 and 72 / 63, 4096 x 4096 73 / 72 and 69 / 65, 6144 x 4096
+// 89 / 91 and 83 / 80, 9728 x 2560 89 / 95 and 79 / 76, 12288 x 4096 127 / 138 and
+// 118 / 124.  Up to 128 rows: the gate alone, 121 rows, 4096 x 8192 59 / 75, 2560 x
+// 5120 46 / 48, 29 rows 2048 x 2048 31 / 30.
+inline bool mlp_dma_gate_rows(long long rows, int d, int I, int ew, bool swiglu, int bigram) {
     if (rows > (bigram ? kMlpDmaMaxRows : kMlpDmaMaxGateRows) || d % 64 != 0 || I % 64 != 0 || ew % 64 != 0) return false;
-    if (rows > kMlpDmaMaxRows && (long long)I * (d + ew) < 30000000) return false;
-    return mlp_dma_plan_ok(mlp_dma_gate_plan((int)rows, d, ew, I, true)) &&
-           mlp_dma_plan_ok(mlp_dma_gate_plan((int)rows, d, ew, I, false));
+    if (rows > kMlpDmaMaxRows && (long long)I * (d + ew) < (swiglu ? 30000000 : 40000000)) return false;
+    return mlp_dma_plan_ok(mlp_dma_gate_plan((int)rows, d, ew, I, swiglu));
 }
-inline bool mlp_dma_gate_applies(bool bf16, int b, int gamma, int R, int d, int I, int ew, int bigram) {
-    return bf16 && (long long)b * gamma <= kMlpDmaMaxStates && mlp_dma_gate_rows((long long)b * R, d, I, ew, bigram);
+inline bool mlp_dma_gate_applies(int b, int gamma, int R, int d, int I, int ew, bool swiglu, int bigram) {
+    return (long long)b * gamma <= kMlpDmaMaxStates && !tile_wide(d + (long long)ew) &&
+           mlp_dma_gate_rows((long long)b * R, d, I, ew, swiglu, bigram);
 }
 inline bool mlp_dma_linear_rows(long long rows, int d) {
     return rows <= kMlpDmaMaxRows && d % 64 == 0 && mlp_dma_plan_ok(mlp_dma_linear_plan((int)rows, d));
@@ -522,10 +527,9 @@ inline Workspace workspace_layout(int b, int gamma, int d, int I, int V, int k, 
                 w.ncounters = w.ncounters > q.items ? w.ncounters : q.items;
             };
             if (mlp_dma_linear_rows(n, d)) need(mlp_dma_linear_plan(n, d));
-            if (!tile_wide(d + (long long)npre * d) && mlp_dma_gate_rows(n, d, I, npre * d, bigram)) {
-                need(mlp_dma_gate_plan(n, d, npre * d, I, true));
-                need(mlp_dma_gate_plan(n, d, npre * d, I, false));
-            }
+            for (const bool swiglu : {true, false})
+                if (!tile_wide(d + (long long)npre * d) && mlp_dma_gate_rows(n, d, I, npre * d, swiglu, bigram))
+                    need(mlp_dma_gate_plan(n, d, npre * d, I, swiglu));
         }
     }
     const size_t lm = lm_reserve_bytes(rows2, V, d, bf16), part = align256(mp * 4);

@@ -77,8 +77,9 @@ static void check_fits(const Shape& s) {
               w.counters - w.hp >= (size_t)rows * s.d * es,
           "rows");
     if (!s.bf16) return;
-    const bool gate = mlp_dma_gate_applies(true, s.b, s.gamma, R, s.d, s.I, ew, s.bigram), wide = tile_wide(s.d + (long long)ew);
-    const size_t erows = s.bigram && !gate && !wide ? (size_t)s.b * bigram_tokens(s.gamma, s.k) : (size_t)rows * npre;
+    const bool wide = tile_wide(s.d + (long long)ew);
+    auto gate = [&](bool swiglu) { return mlp_dma_gate_applies(s.b, s.gamma, R, s.d, s.I, ew, swiglu, s.bigram); };
+    const size_t erows = s.bigram && !gate(true) && !wide ? (size_t)s.b * bigram_tokens(s.gamma, s.k) : (size_t)rows * npre;
     CHECK(w.act - w.et >= erows * s.d * es, "embeddings (b %d gamma %d k %d)", s.b, s.gamma, s.k);
     auto tables = [&](const TilePlan& p, bool paired, int n, long long N, size_t room, const char* what) {
         check_product(p, paired, what, s);
@@ -89,7 +90,7 @@ static void check_fits(const Shape& s) {
               "pieces (rows %d d %d I %d)", rows, s.d, s.I);
     };
     for (int N : {2 * s.I, s.I}) {
-        if (gate && !wide) {
+        if (gate(N == 2 * s.I)) {
             pieces(mlp_dma_gate_plan(rows, s.d, ew, s.I, N == 2 * s.I));
         } else if (s.bigram && !wide) {
             if (N == s.I) continue;
