@@ -262,7 +262,7 @@ struct TilePlan {
 // Tile shapes (WMT, NXT, activation pairs).
 #define TF_TILE_SHAPES(F)                                                                                     \
     F(8, 8, false) F(6, 8, false) F(5, 8, false) F(4, 8, false) F(4, 4, false) F(2, 4, false) F(4, 2, false) \
-    F(8, 4, true) F(4, 4, true) F(2, 4, true) F(4, 2, true)
+    F(8, 4, true) F(4, 4, true) F(2, 4, true) F(4, 2, true) F(2, 2, true)
 
 // The one shape of rows past a descriptor's offsets.
 constexpr int kTileWideW = 4, kTileWideX = 2;
@@ -290,7 +290,10 @@ inline long long tile_split_floats(int rows, long long N, bool wide = false) {
 // (us, 256 CUs): 1936 x 8192 x 4096 256 x 256 106 / 97, 128 x 256 119 / 120,
 // 160 x 256 130 / 130; 455 x 19456 x 2560 160 x 256 55 / 55, 192 x 256 59 / 59, 256 x 256 72 / 67;
 // 256 x 8192 x 4096 128 x 128 in two splits 30 / 30, 64 x 128 33 / 41; pairs:
-// 905 x 4096 x 4096 128 x 128 56 / 51, 256 x 128 in two splits 60 / 62.
+// 905 x 4096 x 4096 128 x 128 56 / 51, 256 x 128 in two splits 60 / 62; at most 64
+// rows 64 x 64, which copies half the bytes of 64 x 128 (the SiLU call from cold
+// weights, 64 x 128 or 128 x 64 / 64 x 64: 1 row x 4096 x 4096 36.2 / 34.7, x 4096 x 12288
+// 78.7 / 73.3, 29 rows x 4096 x 4096 37.6 / 36.0, 61 rows 43.2 / 40.7).
 inline TilePlan tile_plan(int rows, int N, int K, int nseg, bool paired, int max_splits, bool tables,
                           bool wide = false) {
     TilePlan best{};

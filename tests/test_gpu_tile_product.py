@@ -119,6 +119,8 @@ def _check(form, w, rows=None):
     ("swiglu", 1, 16, 8, 128, 4160), ("swiglu", 4, 8, 4, 192, 64), ("silu", 2, 8, 9, 1088, 6208),
     ("swiglu", 1, 16, 16, 2048, 7296), ("swiglu", 1, 16, 16, 2048, 7360),
     ("silu", 1, 16, 16, 2048, 9728), ("silu", 1, 16, 16, 2048, 9792),
+    # down projections of at most 64 rows: 2 x 2, one and eight splits
+    ("silu", 1, 1, 1, 192, 64), ("swiglu", 1, 8, 9, 1024, 3072), ("silu", 2, 3, 4, 80, 2064),
     ("linear", 16, 16, 8, 96, 0),
     ("linear", 16, 16, 8, 2064, 0),     # 5 x 8 in two splits
     ("linear", 16, 16, 8, 4096, 0),     # 4 x 8
