@@ -117,9 +117,15 @@ def _shapes(func: str, **want):
             raise ValueError(f"{func}: {name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
+# the current stream's raw handle without a Stream object (verifier hand-off, two calls: 17.4 -> 14.3 us on the host);
+# torch keeps it private, so a torch without it takes the public way
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
-    # the raw handle: building a Stream object on every call took a good part of a small call's host time
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _check(func: str, status: int):

@@ -257,6 +257,21 @@ def test_build_tree_rejects(over, code):
     assert _tree(**over) == code
 
 
+def test_stream_handle_with_and_without_the_private_call(monkeypatch):
+    import types
+
+    import torch
+    asked = []
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda device: asked.append(str(device)) or types.SimpleNamespace(cuda_stream=17))
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream(torch.device("cuda", 1)) == 17
+    monkeypatch.setattr(binding, "_raw_stream", lambda index: 100 + index)
+    assert binding._stream(torch.device("cuda", 2)) == 102
+    assert binding._stream(torch.device("cuda")) == 17
+    assert asked == ["cuda:1", "cuda"]
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     h = torch.zeros(1, 2, 16, dtype=torch.bfloat16)
