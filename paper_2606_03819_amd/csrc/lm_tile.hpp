@@ -47,7 +47,7 @@ struct EpiLmTile {
 
     // b merged into a
     static __device__ __forceinline__ void merge(List& a, const List& b, float sl2) {
-        const float ma = logit_trunc_inf(a.k[0]), mb = logit_trunc_inf(b.k[0]);
+        const float ma = logit_trunc(a.k[0]), mb = logit_trunc(b.k[0]);
         float drop = fmaxf(a.u, b.u);
         float t[P];
 #pragma unroll
@@ -71,8 +71,6 @@ struct EpiLmTile {
         const float m = fmaxf(ma, mb);
         a.s = a.s * exp2_diff(ma, m, sl2) + b.s * exp2_diff(mb, m, sl2);
     }
-    // logit_trunc that keeps -inf (whose low bits are clear already)
-    static __device__ __forceinline__ float logit_trunc_inf(float k) { return logit_trunc(k); }
 
     template <int J>
     static __device__ __forceinline__ void swap_rows(float& x, float& y) {

@@ -357,9 +357,7 @@ __device__ __forceinline__ void mlp_piece_begin(const MlpDmaArgs& a, int item, i
     // h phase: 32 rows of h~ in four 8-row blocks, block c
     {
         const int row = 8 * c + lrow;
-        sg.hsrc = a.xh != nullptr ? a.xh + (size_t)min(row, a.Rh - 1) * (a.nkh * 64) + 8 * (lslot ^ T::swz128(row)) +
-                                        64 * c0
-                                  : nullptr;
+        sg.hsrc = a.xh + (size_t)min(row, a.Rh - 1) * (a.nkh * 64) + 8 * (lslot ^ T::swz128(row)) + 64 * c0;
     }
     // e phase: DMA instruction q = c + 4v covers rows XRPI*q ..
     const int ce0 = c0 - a.nkh;   // e chunk of the segment's first chunk (negative in the h phase)

@@ -369,10 +369,6 @@ inline TilePlan tile_token_plan(int tokens, int N, int d) { return tile_plan(tok
 #ifndef TF_MLP_DMA_TG_IN
 #define TF_MLP_DMA_TG_IN 4
 #endif
-// items of two tiles without an h phase: no launch makes them now, the checks of the split cover them
-#ifndef TF_MLP_DMA_TG_DOWN
-#define TF_MLP_DMA_TG_DOWN 2
-#endif
 constexpr int kMlpDmaMinUnits = 12;
 constexpr int kMlpDmaMaxRows = 128;    // conditional rows (four activation tiles)
 constexpr int kMlpDmaMaxGateRows = 256; // the input projections alone (eight activation tiles)
@@ -403,8 +399,8 @@ inline MlpDmaPlan mlp_dma_plan(int rows, int ntiles, int nkh, int nke, int TG) {
     // 3:2 and 9:5); two tiles take a ratio between that and 1, and one tile,
     // like the h phase, costs the same; eight tiles (the input
     // projections of 129-256 rows) 5:2.
-    p.wh = nkh == 0 ? 1 : (p.NTE == 8 ? 2 : (p.NTE == 4 ? 3 : (p.NTE == 2 ? 4 : 1)));
-    p.we = nkh == 0 ? 1 : (p.NTE == 8 ? 5 : (p.NTE == 4 ? 5 : (p.NTE == 2 ? 5 : 1)));
+    p.wh = p.NTE == 8 ? 2 : (p.NTE == 4 ? 3 : (p.NTE == 2 ? 4 : 1));
+    p.we = p.NTE == 1 ? 1 : 5;
     if (!cost_split_valid(p.items, nkh, nke, p.wh, p.we, p.G)) p.wh = p.we = 1;
     return p;
 }

@@ -19,7 +19,7 @@ struct GemmShape {
 // One-row-block products (every activation row in one block): an item's k-
 // chunks come in two phases, first nkh chunks of the h~ half of x against the
 // drafter states' one row tile, then nke chunks against every row (the e~
-// half, or the whole input of a product without the split).  An e chunk costs
+// half).  An e chunk costs
 // more than an h chunk (more activation tiles per weight byte), so the units
 // (item-major: item, then chunk) are dealt out by cost: an h chunk costs wh, an e
 // chunk we, and workgroup g owns the units whose cost offset falls in
@@ -79,8 +79,8 @@ __host__ __device__ inline CutPieces cut_pieces(const CostSplit& s, int item) {
     p.gfirst = unit_owner(s, item, 0);
     p.npieces = unit_owner(s, item, s.nk - 1) - p.gfirst + 1;
     p.slot0 = 2 * p.gfirst + (unit_start(s, p.gfirst) < item * s.nk ? 1 : 0);
-    p.ph1 = s.nkh > 0 ? unit_owner(s, item, (s.nkh < s.nk ? s.nkh : s.nk) - 1) - p.gfirst + 1 : 0;
-    p.pe0 = s.nkh < s.nk ? unit_owner(s, item, s.nkh) - p.gfirst : p.npieces;
+    p.ph1 = unit_owner(s, item, s.nkh - 1) - p.gfirst + 1;
+    p.pe0 = unit_owner(s, item, s.nkh) - p.gfirst;
     return p;
 }
 

@@ -89,9 +89,8 @@ int main() {
                 for (int npre = 1; npre <= 2; ++npre) {
                     check(rows, cdiv(I, 16), d / 64, npre * d / 64, TF_MLP_DMA_TG_IN, nitems);   // gate/up
                     check(rows, cdiv(I, 32), d / 64, npre * d / 64, TF_MLP_DMA_TG_IN, nitems);   // SiLU gate
-                    check(rows, cdiv(d, 32), 0, I / 64, TF_MLP_DMA_TG_DOWN, nitems);            // down
                     check(rows, cdiv(d, 32), d / 64, d / 64, TF_MLP_DMA_TG_IN, nitems);          // linear
-                    nplans += 4;
+                    nplans += 3;
                 }
     std::printf("%lld plans, %lld items, %d failures\n", nplans, nitems, fails);
     return fails != 0;
