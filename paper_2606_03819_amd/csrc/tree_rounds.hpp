@@ -73,11 +73,11 @@ inline size_t pool_lds_bytes(int Rs, int K2, int ncand) {
     return kPoolFixed + (size_t)4 * ncand + (size_t)4 * Rs * pool_ranks(Rs, K2, ncand);
 }
 
-// Selection in rounds from 65 to 512 nodes.  One sequence of 121 rows, us, serial / rounds: peaked rows, 32 nodes
-// 17 / 26, 48 25 / 34, 64 32 / 31, 65 43 / 31, 96 63 / 40, 128 83 / 46, 256 256 / 48, 512 789 / 81; star-shaped trees,
-// 65 nodes 5.1 / 3.3, 128 7.1 / 3.8, 256 16 / 4.8, 512 (not all of a row staged) 30 / 21; rows of fewer entries than
-// nodes, peaked, 32 entries and 128 nodes 81 / 49, 16 and 256 202 / 57.  Flat rows one entry short of the budget are
-// the worst left: 64 and 65 5.1 / 13.7.
+// Selection in rounds from 65 to 512 nodes.  One sequence of 121 rows, us, serial / rounds: peaked rows, 65 nodes
+// 43 / 29, 96 63 / 38, 128 83 / 44, 256 256 / 47, 512 790 / 78 (48 25 / 34 and 64 32 / 31 while the first row's entries
+// took a round of their own); star-shaped trees, 65 nodes 5.1 / 3.5, 128 7.1 / 4.0, 256 16 / 5.0, 512 30 / 9.0; one of
+// 128 nodes with 13 below the first row's 9.9 / 10.7; rows of fewer entries than nodes, peaked, 32 entries and 128
+// nodes 81 / 50, 16 and 256 202 / 58.  Flat rows one entry short of the budget are the worst left: 64 and 65 5.1 / 13.9.
 constexpr int kPoolMinBudget = 65, kPoolMaxBudget = 512;
 inline bool tree_takes_rounds(int B, int Rs, int K2, int ncand) {
     return B >= kPoolMinBudget && B <= kPoolMaxBudget && pool_ranks(Rs, K2, ncand) >= 1 && Rs < 65535;
@@ -92,7 +92,7 @@ struct Pool {
     uint32_t* bins;    // histogram; reused for the renumbering
     uint16_t* place;
     uint32_t* tot;     // 3 x 16 wave totals
-    int* word;         // [0] pool size, [1] bin, [2] rows in order so far, [3] nodes to expand, [4] no star
+    int* word;         // [0] pool size, [1] bin, [2] rows in order so far, [3] nodes to expand, [4] rows to open
     int* tk;
     float* lp;         // [Rs][P]
 };
@@ -136,7 +136,7 @@ __device__ inline bool pool_tie_before(const Pool& p, int x, int y) {
     return (lx & 0xffff) < (ly & 0xffff);
 }
 
-static_assert(kMaxTopk <= kTreeThreads, "a thread a row of depth 2");
+static_assert(kPoolMaxBudget <= kTreeThreads && kPoolMaxBudget < kPoolCap, "a thread an entry of the first row");
 
 // Selects a sequence's tree; false (for the whole workgroup, nothing written)
 // when the rows or their ties call for the serial selection.
@@ -165,14 +165,15 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
     const int32_t* ridx = a.cond_idx + (size_t)seq * nent;
     // the rows' leading log-probs (all of them where they fit) and the candidates
     if (tid == 0) {
-        p.word[0] = 1;
+        p.word[0] = K2 >= a.B ? 1 + a.B : 1;
         p.word[2] = 1;
         p.word[3] = 0;
         p.word[4] = 0;
         p.score[0] = 0.f;   // the root: entry 0
         p.link[0] = 0;
-        p.info[0] = (1u << 16) | kSeen;
+        p.info[0] = (1u << 16) | kSeen | (K2 >= a.B ? kDone : 0u);
     }
+    const int tok0 = tid < min(K2, a.B) ? ridx[tid] : -1;
     for (int e = tid; e < ncand; e += kTreeThreads) p.tk[e] = a.topk[(size_t)seq * ncand + e];
     for (int e0 = tid; e0 < ncache; e0 += 8 * kTreeThreads) {
         float v[8];
@@ -195,35 +196,47 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
     // no such bound: at a threshold above the root's 0, or none, nothing would be taken and nothing checked
     if (K2 >= a.B && !(edge <= 0.f)) return false;
     float tau = K2 >= a.B ? 0.f + edge : neg_inf();
-    // A star-shaped tree: no row that a first pop could open starts above the first row's B-th entry, so that row's
-    // first B entries are the tree (flat rows, as random weights make them).  Looked for where the staged ranks show
-    // it; the serial selection takes such trees in a few sibling runs, and the rounds took twice as long.
-    if (P >= a.B) {
-        const int below = a.gamma < 2 ? 0 : a.mode == kTreeMarginal ? 1 : a.M;   // rows of depth 2: 1 ..
-        const bool sorted = tid >= a.B || p.lp[tid] <= (tid > 0 ? p.lp[tid - 1] : 0.f);
-        if (!sorted || (tid < below && !(0.f + p.lp[0] + p.lp[(1 + tid) * P] < tau))) p.word[4] = 1;
+    int n = 1;
+    // Where the first row bounds the tree, its first B entries are in play from the start.  A star-shaped tree is
+    // those alone: none of them opens a row that starts above the B-th, by their tokens (random weights seldom rank
+    // a candidate there) or by the scores.  It is written at once; the serial selection takes it in a few sibling
+    // runs, and the rounds took twice as long.
+    if (K2 >= a.B) {
+        float s = 0.f;
+        int crow = -1;
+        if (tid < a.B) {
+            const float v = get_lp(0, tid);
+            s = 0.f + v;
+            if (!(v <= (tid > 0 ? get_lp(0, tid - 1) : 0.f))) p.word[2] = 0;   // not in order
+            if (a.mode == kTreeMarginal)
+                crow = a.gamma > 1 ? 1 : -1;
+            else if (a.gamma > 1)
+                for (int m = a.M - 1; m >= 0; --m) crow = p.tk[m] == tok0 ? 1 + m : crow;
+            const bool opens = crow >= 0 && !(s + get_lp(crow, 0) < tau);
+            if (opens) p.word[4] = 1;
+            p.score[1 + tid] = s;
+            p.link[1 + tid] = (uint32_t)tid;
+            p.info[1 + tid] = (uint32_t)(crow + 1) << 16 | 1u << 8 | kSeen | (opens ? 0u : kDone);
+        }
         __syncthreads();
+        if (p.word[2] == 0) return false;
         if (p.word[4] == 0) {
             if (tid < a.B) {
-                const int tok = ridx[tid];
-                int crow = a.mode == kTreeMarginal && below > 0 ? 1 : -1;
-                if (a.mode != kTreeMarginal)
-                    for (int m = below - 1; m >= 0; --m) crow = p.tk[m] == tok ? 1 + m : crow;
                 const size_t o = (size_t)seq * a.B + tid;
-                a.tok[o] = tok;
+                a.tok[o] = tok0;
                 a.par[o] = -1;
                 a.dep[o] = 1;
-                a.score[o] = 0.f + p.lp[tid];
+                a.score[o] = s;
                 if (a.crow != nullptr) a.crow[o] = crow;
             }
             return true;
         }
+        n = 1 + a.B;
     }
     float scale = 1000.f / fminf(fmaxf(-edge, 1e-3f), 1e6f);   // bins of the score, finer as tau rises
     // rows of fewer than B entries do not bound the B-th best, which lies rows deeper: left out of the bins it leaves
     // the threshold open, and the pool overflows with nodes of no use
     if (K2 < a.B) scale *= 0.0625f;
-    int n = 1;
     bool packed = false;
     uint32_t total;
 
@@ -311,9 +324,8 @@ __device__ bool tree_rounds(const TreeArgs& a, int seq, unsigned char* dyn) {
                         hi = mid;
                 }
                 cnt[q] = (uint32_t)lo;
-                // the first child below tau ends what the serial selection may pop, unless it is no number;
-                // the root's prefix holds the entry that tau was taken from
-                if ((lo < K2 && !(get_lp(crow, lo) <= 0.f)) || (round == 0 && K2 >= a.B && lo < a.B)) p.word[2] = 0;
+                // the first child below tau ends what the serial selection may pop, unless it is no number
+                if (lo < K2 && !(get_lp(crow, lo) <= 0.f)) p.word[2] = 0;
                 if (lo == 0) in |= kDone;   // tau only rises
             }
             p.info[e] = in;

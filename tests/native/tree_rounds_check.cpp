@@ -34,7 +34,7 @@ static ucontext_t home, ctx[N];   // a fiber's first entry; later switches are j
 static jmp_buf home_at, at[N];
 static bool entered[N];
 static State state[N];
-static int cur, posted[N], fetched[N], ctrl[N];
+static int cur, posted[N], fetched[N], ctrl[N], barriers;
 static std::vector<char> stacks((size_t)N * 49152);
 static struct { int x; } tid;
 static void yield(State s) {
@@ -73,6 +73,7 @@ static void entry() {
 }
 static void run(void (*f)(), std::mt19937& rng) {
     body = f;
+    barriers = 0;
     for (int t = 0; t < N; ++t) {
         getcontext(&ctx[t]);
         ctx[t].uc_stack.ss_sp = stacks.data() + (size_t)t * 49152;
@@ -111,6 +112,7 @@ static void run(void (*f)(), std::mt19937& rng) {
             std::printf("%d threads at a barrier, %d ended\n", nb, nd);
             exit(1);
         }
+        ++barriers;
         for (int t = 0; t < N; ++t) state[t] = kRun;
     }
 }
@@ -221,6 +223,8 @@ static Case make(int mode, int gamma, int M, int K2, int B, const char* shape) {
         for (int i = 0; i < K2; ++i) toks.push_back(5000 + i);
         toks.resize(K2);
         if (r % 3 == 0) std::shuffle(toks.begin(), toks.end(), rng);
+        if (sh == "closed" && r == 0)   // the first candidates come past the B-th entry, or not at all
+            for (int i = 0; i < std::min(K2, B); ++i) toks[i] = 9500 + i;
         c.idx.insert(c.idx.end(), toks.begin(), toks.end());
         std::vector<float> l(K2);
         const float slope = uniform(0.6f, 2.f);
@@ -247,7 +251,7 @@ static TreeArgs g_args;
 static unsigned char* g_dyn;
 static bool g_ret[emu::N];
 
-// want: 1 must finish, 0 must be handed over, -1 either
+// want: 2 must finish before the first round, 1 must finish, 0 must be handed over, -1 either
 static void check(const Case& c, const char* shape, int want) {
     ++cases;
     const int ncand = c.mode == kTreeMarginal ? 0 : c.gamma * c.M;
@@ -269,7 +273,8 @@ static void check(const Case& c, const char* shape, int want) {
     for (int t = 1; t < emu::N; ++t)
         if (g_ret[t] != g_ret[0]) return fail("threads disagree");
     finished += g_ret[0];
-    if (want >= 0 && g_ret[0] != (want == 1)) return fail(want ? "handed over" : "not handed over");
+    if (want >= 0 && g_ret[0] != (want >= 1)) return fail(want ? "handed over" : "not handed over");
+    if (want == 2 && emu::barriers > 2) return fail("a star-shaped tree selected in rounds");
     if (!g_ret[0]) return;
     const std::vector<Node> w = walk(c);
     for (int i = 0; i < c.B; ++i) {
@@ -294,6 +299,11 @@ int main() {
             for (const char* sh : {"peaked", "flat", "mixed", "tail"}) {
                 // rows of fewer than B entries give no threshold to start from, and may overflow the pool
                 check(make(mode, s.gamma, s.M, s.K2, s.B, sh), sh, sh[0] != 't' ? 1 : -1);
+            }
+            // a first row that opens none, or bounds all, of the rows below
+            if (s.K2 >= s.B) {
+                check(make(mode, s.gamma, s.M, s.K2, s.B, "flat"), "flat", 2);
+                if (mode != kTreeMarginal) check(make(mode, s.gamma, s.M, s.K2, s.B, "closed"), "closed", 2);
             }
             for (const char* sh : {"ties", "zeros", "allzero", "edge", "impossible"})
                 check(make(mode, s.gamma, s.M, s.K2, s.B, sh), sh, -1);

@@ -58,6 +58,8 @@ def _case(shape, gamma, k, K2, seed, marginal, bigram=False):
         idx[r] = np.concatenate([rng.permutation(topk[depth[r]]), rest])[:K2]
         if r % 3 == 0:
             idx[r] = rng.permutation(idx[r])
+    if shape == "closed":   # no candidate among the first row's entries: the tree is these alone
+        idx[0] = np.arange(20000, 20000 + K2)
     lp = -1.2 * np.log1p(np.arange(K2))[None] * rng.uniform(0.6, 2.0, (R, 1)) - 0.3 + 0.3 * rng.standard_normal((R, K2))
     lp = np.minimum(lp, -1e-3)
     if shape == "flat":
@@ -84,6 +86,7 @@ def _case(shape, gamma, k, K2, seed, marginal, bigram=False):
     ("peaked", 16, 8, 16, 256), ("flat", 16, 8, 32, 128), ("peaked", 16, 8, 32, 512), ("flat", 4, 8, 64, 65),
     # star-shaped trees: the first row's entries alone
     ("flat", 16, 8, 65, 65), ("flat", 16, 8, 128, 128), ("flat", 1, 4, 100, 100), ("flat", 12, 40, 200, 130),
+    ("closed", 16, 8, 65, 65), ("closed", 16, 8, 512, 512), ("closed", 3, 4, 200, 130),
     ("tail", 6, 4, 100, 300), ("unsorted", 8, 4, 100, 100), ("positive", 8, 4, 100, 100), ("unsorted", 16, 20, 70, 70),
 ])
 @pytest.mark.parametrize("marginal", [False, True])
@@ -111,6 +114,7 @@ def test_rounds_pop_what_the_walk_pops(shape, gamma, k, K2, B, marginal):
 @pytest.mark.parametrize("shape,gamma,k,K2,B", [
     ("peaked", 8, 4, 100, 100), ("peaked", 16, 8, 128, 128), ("peaked", 1, 4, 300, 300), ("peaked", 2, 5, 100, 90),
     ("ties", 6, 4, 80, 80), ("peaked", 5, 12, 256, 512), ("flat", 7, 5, 65, 65), ("unsorted", 8, 4, 100, 100),
+    ("closed", 8, 4, 100, 100),
 ])
 def test_bigram_rounds_pop_what_the_walk_pops(shape, gamma, k, K2, B):
     import torch
